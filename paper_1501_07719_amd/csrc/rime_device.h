@@ -234,6 +234,47 @@ __device__ inline double sumsq_rn(double a, double b) {
   return a * a + b * b;
 }
 
+// The per-antenna term of one (antenna, source) at channel c: a = e K and, for
+// the adjoint, k3 with d ln e / d(l, m) = k3 (l - dl_p, m - dm_p).  The angles
+// are formed in float64 and their sines and cosines to within about a unit of
+// R (N::sincos_turns): each factor is reused by every baseline that holds the
+// antenna.  r2b and rb: squared distance to the pointing centre and its root.
+template <class R, bool WITH_BETA>
+__device__ inline void antenna_term(const KParams &p, const PhaseArg<sizeof(R) == 8> &tau,
+                                    double r2b, double rb, int c, typename Num<R>::R2 &a, R &k3) {
+  using N = Num<R>;
+  const double r = tau.turns(p.nu_c[c]);
+  R sn, cs;
+  N::sincos_turns(r, &sn, &cs);
+  R e = R(1);
+  k3 = R(0);
+  if (p.beam) {
+    // x_b = bs r, bs = beam_k nu / beam_ref_freq, clipped at beam_clip
+    // (eq. e_term); the clip is decided on r^2 against the per-channel
+    // threshold (beam_clip / bs)^2.
+    // d ln e / dl = -3 tan(x) dx/dl, dx/dl = bs (l - dl_p) / r
+    //             = -3 bs^2 (l - dl_p) tan(x)/x ; zero past the clip.
+    const double bs = p.bsc[c];
+    const bool clipped = r2b >= p.clip_r2[c];
+    const double xr = clipped ? p.beam_clip : bs * rb;
+    R tx = R(0);
+    if constexpr (sizeof(R) == 8) {
+      R sb, cb;
+      N::sincos_turns(xr * kInvTwoPi, &sb, &cb);
+      e = cb * cb * cb;
+      if (WITH_BETA && !clipped)
+        tx = xr > 1e-4 ? sb * N::rcp(cb * xr) : R(1) + xr * xr * R(1.0 / 3.0);
+    } else {
+      float txf = 0.0f;
+      beam_f32(static_cast<float>(xr), WITH_BETA, &e, &txf);
+      if (!clipped) tx = txf;
+    }
+    if (WITH_BETA) k3 = static_cast<R>(p.bk3[c]) * tx;
+  }
+  a.x = e * cs;
+  a.y = -e * sn;
+}
+
 // Compensated float64 accumulator.
 struct Comp {
   double s = 0.0, c = 0.0;
@@ -278,6 +319,36 @@ __device__ inline Comp block_reduce(Comp v, double2 *scratch) {
     r = wave_reduce(r);
   }
   return r;
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs; renumbering them makes
+// consecutive work items (which share operands through L2) land on one XCD.
+__device__ inline int xcd_item(int nitems) {
+  const int per_xcd = (nitems + 7) / 8;
+  return static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+}
+
+// St'_k (k = I, Q, U, V) of source s of the set at channel c and timestep t:
+// the spectrally scaled Stokes vector, or, with brightness per timestep (ST),
+// the spectral factor times that timestep's Stokes vector (rounded as in the
+// per-baseline kernels).  The kernels that call it per chunk take ST as a
+// template parameter, so that the plain calls do not carry its registers.
+template <bool ST, class R>
+__device__ inline typename Num<R>::R4 pme_stokes(const KParams &p, int s, int c, int t) {
+  using R4 = typename Num<R>::R4;
+  const int64_t gs = p.one.src_off + s;
+  if (ST) {
+    const int nsrc = p.one.npsrc + p.one.ngsrc + p.one.nxsrc;
+    const double *q = p.stokes_t + (static_cast<int64_t>(t) * nsrc + s) * 4;
+    const double f = static_cast<double>(static_cast<const R *>(p.src_sf)[gs * p.nchan + c]);
+    R4 v;
+    v.x = static_cast<R>(f * q[0]);
+    v.y = static_cast<R>(f * q[1]);
+    v.z = static_cast<R>(f * q[2]);
+    v.w = static_cast<R>(f * q[3]);
+    return v;
+  }
+  return static_cast<const R4 *>(p.src_st)[gs * p.nchan + c];
 }
 
 constexpr int nat_for(int nbt) { return nbt >= 1024 ? 64 : nbt >= 256 ? 32 : 16; }

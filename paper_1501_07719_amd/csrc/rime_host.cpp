@@ -24,6 +24,7 @@ hipError_t launch_pme(const KParams &p, hipStream_t stream);
 hipError_t launch_pme_adjoint(const KParams &p, bool phase, hipStream_t stream);
 hipError_t launch_pme_finalize(const KParams &p, hipStream_t stream);
 hipError_t launch_pme_scale(const KParams &p, hipStream_t stream);
+hipError_t launch_planes(const KParams &p, hipStream_t stream);
 int variant_count(int mode, int prec);
 const Variant *variant_info(int mode, int prec, int index);
 hipError_t launch_variant(int mode, int prec, int index, const KParams &p, int nitems,
@@ -314,10 +315,11 @@ struct WsLayout {
   size_t dom = 0;
   size_t die_part = 0, src_sf = 0, gst = 0;
   size_t geo = 0, lon = 0, st = 0, gs = 0, rec = 0, chi2 = 0, grad = 0, grad2 = 0;
-  size_t ph_hi = 0, ph_lo = 0, ph_k3 = 0, spts = 0, pexp = 0, rho_t = 0, pgrad = 0;
+  size_t ph_hi = 0, spts = 0, pexp = 0, rho_t = 0, pgrad = 0;
   size_t src_f = 0, mfrag = 0, mscale = 0, rho_g = 0, pfin = 0;
   int32_t pme_tchunk = 0;  // timesteps per phase-plane pass (0: engine off)
   bool pme_adj = false;    // point-source adjoint on the matrix cores
+  bool has_k3 = false;     // the planes carry the beam-gradient factor
   size_t total = 0;
 };
 
@@ -394,10 +396,9 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
     const size_t per_t = plane_t * (k3 ? 3 : 2) + frag_t;
     L.pme_tchunk = static_cast<int32_t>(
         std::max<size_t>(1, std::min<size_t>(plan->ntime, kPmePlaneBytes / per_t)));
+    L.has_k3 = k3;
     L.ph_hi = off;
-    off += align_up(plane_t * L.pme_tchunk);
-    L.ph_lo = off;
-    off += align_up(plane_t * L.pme_tchunk);
+    off += align_up(plane_t * (k3 ? 3 : 2) * L.pme_tchunk) + 4 * kAlign;
     if (fwd_sums) {
       L.spts = off;
       off += align_up(static_cast<size_t>(plan->ntime) * plan->nchan * plan->npair * 4 *
@@ -407,10 +408,6 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
     }
     if (adj) {
       L.pme_adj = true;
-      if (k3) {
-        L.ph_k3 = off;
-        off += align_up(plane_t * L.pme_tchunk);
-      }
       L.rho_t = off;
       off += align_up(static_cast<size_t>(plan->ntime) * plan->nchan * plan->npair * 4 *
                       kPmeBlk * kPmeBlk * sizeof(float2));
@@ -613,6 +610,45 @@ struct Call {
   }
 };
 
+// Divides the plane region of the fp16 engine: hi and lo planes of the point
+// sources (and their k3 in gradient mode), then the float32 planes of the
+// extended sources that rime_main stages from.  Both take the same bytes per
+// source, so the region, sized for the call's sources, holds any split.
+// Extended sources get planes in the forward-only modes of the 256-thread
+// kernels when one pass over time holds them all: there every antenna's terms
+// would be formed by (tiles per antenna) workgroups (64 antennas, 500
+// Gaussians, 6400 (timestep, channel): 4 times; the kernel takes 4.26 ms with
+// planes, which take 0.52 ms, and 5.79 ms without).  The planes cost a launch
+// of about 6 us, which these kernels save from about 2^24 terms formed in
+// workgroups on (84 antennas, 29 Gaussians, 10 (timestep, channel): 38.4
+// against 36.4 us without planes).  In the gradient modes (1024 threads, half
+// the tiles per antenna, most of the time in the adjoint) they do not pay: 12
+// proposals over 64 antennas, 50 timesteps, 32 channels 42.5 against 42.0 ms.
+void carve_planes(const rime_plan *plan, const Call &c, const Variant &v, const WsLayout &L,
+                  char *w, KParams &p) {
+  const size_t per_src = static_cast<size_t>(plan->nchan) * plan->nap * L.pme_tchunk * 4;
+  size_t off = L.ph_hi;
+  auto take = [&](size_t bytes) {
+    char *r = w + off;
+    off += align_up(bytes);
+    return r;
+  };
+  p.ph_hi = reinterpret_cast<uint32_t *>(take(per_src * c.one.npsrc));
+  p.ph_lo = reinterpret_cast<uint32_t *>(take(per_src * c.one.npsrc));
+  if (L.has_k3) p.ph_k3 = reinterpret_cast<float *>(take(per_src * c.one.npsrc));
+  const int next = c.max_nsrc - c.one.npsrc;
+  const int64_t staged = static_cast<int64_t>(plan->tiles[nbt_slot(v.threads)].ntile) *
+                         nat_for_host(v.threads) * plan->ntime * plan->nchan * next;
+  if (staged >= (int64_t(1) << 24) && c.mode != RIME_MODE_CHI2_GRAD &&
+      L.pme_tchunk >= plan->ntime && v.nc == 2 && v.threads == 256) {
+    p.pl_s0 = c.one.npsrc;
+    p.pl_ns = next;
+    p.pl_a = reinterpret_cast<float2 *>(take(2 * per_src * next));
+    p.pme_t0 = 0;
+    p.pme_nt = plan->ntime;
+  }
+}
+
 // Kernel parameters of one launch geometry over workspace region `w` laid out
 // by L (matrix-core fields set when L enables the engine).
 KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, const Geometry &g,
@@ -673,17 +709,18 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
     p.gst_part = reinterpret_cast<double *>(w + L.gst);
   p.pme = 0;
   p.pme_adj = 0;
+  if (L.pme_tchunk > 0) {
+    p.nap = plan->nap;
+    carve_planes(plan, c, v, L, w, p);
+  }
   if (L.pme_tchunk > 0 && c.one.npsrc > 0) {
     p.pme = 1;
-    p.nap = plan->nap;
     p.npair = plan->npair;
     p.pair_blk = plan->d_pair_blk;
     p.bl_slot = plan->d_bl_slot;
     p.ngroup = plan->ngroup;
     p.pme_pairs = plan->pme_pairs;
     p.groups = plan->d_groups;
-    p.ph_hi = reinterpret_cast<uint32_t *>(w + L.ph_hi);
-    p.ph_lo = reinterpret_cast<uint32_t *>(w + L.ph_lo);
     p.spts = reinterpret_cast<double2 *>(w + L.spts);
     p.pme_exp = reinterpret_cast<int32_t *>(w + L.pexp);
     if (L.pme_adj) {
@@ -710,9 +747,8 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
 // The point-source adjoint on the matrix cores, in passes over time that
 // each rebuild their phase planes unless `reuse` (one pass whose planes the
 // forward left in place).
-rime_status enqueue_pme_adjoint(const rime_plan *plan, KParams p, const WsLayout &L, char *w,
-                                bool reuse, hipStream_t stream) {
-  if (L.ph_k3) p.ph_k3 = reinterpret_cast<float *>(w + L.ph_k3);
+rime_status enqueue_pme_adjoint(const rime_plan *plan, KParams p, const WsLayout &L, bool reuse,
+                                hipStream_t stream) {
   for (int t0 = 0; t0 < plan->ntime; t0 += L.pme_tchunk) {
     p.pme_t0 = t0;
     p.pme_nt = std::min(L.pme_tchunk, plan->ntime - t0);
@@ -771,7 +807,7 @@ rime_status enqueue_res64(const rime_plan *plan, const Call &c, int vidx, void *
   if (events && plan->ev_main1) RIME_HIP(hipEventRecord(plan->ev_main1, stream));
   if (grad) {
     if (pa.pme_adj) {
-      const rime_status st = enqueue_pme_adjoint(plan, pa, R.a, w + R.a_off, false, stream);
+      const rime_status st = enqueue_pme_adjoint(plan, pa, R.a, false, stream);
       if (st != RIME_OK) return st;
     }
     RIME_HIP(launch_adj(vidx, pa, static_cast<int>(na), stream));
@@ -809,21 +845,20 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
     KParams pf = p;
     // with one pass over time the adjoint reuses the forward's phase planes,
     // which then carry the beam-derivative plane too
-    pf.ph_k3 = (L.pme_adj && L.ph_k3 && L.pme_tchunk >= plan->ntime)
-                   ? reinterpret_cast<float *>(w + L.ph_k3)
-                   : nullptr;
+    if (L.pme_tchunk < plan->ntime) pf.ph_k3 = nullptr;
     for (int t0 = 0; t0 < plan->ntime; t0 += L.pme_tchunk) {
       pf.pme_t0 = t0;
       pf.pme_nt = std::min(L.pme_tchunk, plan->ntime - t0);
       RIME_HIP(launch_pme(pf, stream));
     }
   }
+  if (p.pl_a) RIME_HIP(launch_planes(p, stream));
   if (events && plan->ev_main0) RIME_HIP(hipEventRecord(plan->ev_main0, stream));
   RIME_HIP(launch_variant(mode, prec, vidx, p, static_cast<int>(nitems), stream));
   if (events && plan->ev_main1) RIME_HIP(hipEventRecord(plan->ev_main1, stream));
   if (p.pme_adj) {
     const rime_status st =
-        enqueue_pme_adjoint(plan, p, L, w, L.pme_tchunk >= plan->ntime, stream);
+        enqueue_pme_adjoint(plan, p, L, L.pme_tchunk >= plan->ntime, stream);
     if (st != RIME_OK) return st;
   }
   if (events && plan->ev_stop) RIME_HIP(hipEventRecord(plan->ev_stop, stream));

@@ -149,6 +149,10 @@ struct KParams {
   int32_t pme_fchunk;      // item chunks of those sums
   uint4 *mfrag;            // [pme_nt][nchan][nblk][nqr][4][8][64][2] fp16 fragments of M
   float *mscale;           // [pme_nt][nchan][nblk][nqr] 2^e undoing the fragment scale
+  // float32 planes of the extended sources (pl_ns from pl_s0 on), a_ps = e_ps K_ps
+  // [pme_nt][nchan][pl_ns][nap], or nullptr: rime_main stages from them
+  float2 *pl_a;
+  int32_t pl_s0, pl_ns;
 };
 
 // Antenna block of the matrix-core engine (rows and columns of one MFMA tile),

@@ -205,7 +205,7 @@ struct Layout {
 // Per-antenna stage for one source tile: a[s][ant][c] = e K (and, for the
 // adjoint, beta[s][ant][c] = d ln e / d(l, m)), plus the tile's scaled Stokes
 // and Gaussian shapes.
-template <class R, int NBT, int NC, int NS, int MODE, bool WITH_BETA, bool TERMS>
+template <class R, int NBT, int NC, int NS, int MODE, bool WITH_BETA, bool TERMS, bool PL>
 __device__ inline void stage_tile(const KParams &p, const SetDesc &sd, int t, int tile, int s0,
                                   int cnt, bool shaped, int c0, int ncv,
                                   const double (*s_uvw)[3],
@@ -217,78 +217,80 @@ __device__ inline void stage_tile(const KParams &p, const SetDesc &sd, int t, in
   using R4 = typename N::R4;
   constexpr int NAT = L::NAT;
   const int tid = threadIdx.x;
-  for (int idx = tid; idx < NS * NAT; idx += NBT) {
-    const int s = idx / NAT;
-    const int ai = idx - s * NAT;
-    const bool ok = s < cnt && p.tile_ant[tile * NAT + ai] >= 0;
-    R2 out[NC];
-    R2 bet[NC];
+  if constexpr (PL) {
+    // the terms come from the planes; all loads of a thread are issued before
+    // the first one is used
+    static_assert(!WITH_BETA && NS * NAT % NBT == 0, "whole rounds, forward only");
+    const int64_t plane = static_cast<int64_t>(p.pl_ns) * p.nap;
+    const float2 *pa = p.pl_a +
+                       (static_cast<int64_t>(t - p.pme_t0) * p.nchan + c0) * plane +
+                       static_cast<int64_t>(s0 - p.pl_s0) * p.nap;
+    constexpr int NI = NS * NAT / NBT;
+    R2 va[NI][NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      out[c].x = R(0);
-      out[c].y = R(0);
-      bet[c].x = R(0);
-      bet[c].y = R(0);
-    }
-    if (ok) {
-      const double4 g = p.src_geo[sd.src_off + s0 + s];
-      // tau = u l + v m + w (n - 1), metres (eq. k_term): error-free in
-      // float64, a plain float64 evaluation for the float32 path
-      const PhaseArg<sizeof(R) == 8> tau(s_uvw[ai][0], s_uvw[ai][1], s_uvw[ai][2], g.x, g.y,
-                                         g.z);
-      double r2b = 0.0, dl = 0.0, dm = 0.0, rb = 0.0;
-      if (p.beam) {
-        dl = g.x - s_pnt[ai][0];
-        dm = g.y - s_pnt[ai][1];
-        r2b = sumsq_rn(dl, dm);
-        rb = sqrt(r2b);
-      }
-      // The angles of the per-antenna factors are formed in float64 and their
-      // sines and cosines to within about a unit of R (N::sincos_turns): each
-      // factor is reused by every baseline of the tile that holds the antenna.
+    for (int i = 0; i < NI; ++i) {
+      const int idx = tid + i * NBT;
+      const int s = idx / NAT, ai = idx - s * NAT;
+      const int ant = p.tile_ant[tile * NAT + ai];
+      const bool ok = s < cnt && ant >= 0;
+      const int64_t o = static_cast<int64_t>(s) * p.nap + ant;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        if (c < ncv) {
-          const double r = tau.turns(p.nu_c[c0 + c]);
-          R sn, cs;
-          N::sincos_turns(r, &sn, &cs);
-          R e = R(1);
-          if (p.beam) {
-            // x_b = bs r, bs = beam_k nu / beam_ref_freq, clipped at beam_clip
-            // (eq. e_term); the clip is decided on r^2 against the per-channel
-            // threshold (beam_clip / bs)^2.
-            // d ln e / dl = -3 tan(x) dx/dl, dx/dl = bs (l - dl_p) / r
-            //             = -3 bs^2 (l - dl_p) tan(x)/x ; zero past the clip.
-            const double bs = p.bsc[c0 + c];
-            const bool clipped = r2b >= p.clip_r2[c0 + c];
-            const double xr = clipped ? p.beam_clip : bs * rb;
-            R tx = R(0);
-            if constexpr (sizeof(R) == 8) {
-              R sb, cb;
-              N::sincos_turns(xr * kInvTwoPi, &sb, &cb);
-              e = cb * cb * cb;
-              if (WITH_BETA && !clipped)
-                tx = xr > 1e-4 ? sb * N::rcp(cb * xr) : R(1) + xr * xr * R(1.0 / 3.0);
-            } else {
-              float txf = 0.0f;
-              beam_f32(static_cast<float>(xr), WITH_BETA, &e, &txf);
-              if (!clipped) tx = txf;
-            }
+        va[i][c].x = va[i][c].y = R(0);
+        if (ok && c < ncv) va[i][c] = pa[c * plane + o];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int idx = tid + i * NBT;
+      const int s = idx / NAT, ai = idx - s * NAT;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) s_a[s * L::AST + ai * NC + c] = va[i][c];
+    }
+  } else {
+    for (int idx = tid; idx < NS * NAT; idx += NBT) {
+      const int s = idx / NAT;
+      const int ai = idx - s * NAT;
+      const bool ok = s < cnt && p.tile_ant[tile * NAT + ai] >= 0;
+      R2 out[NC];
+      R2 bet[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        out[c].x = R(0);
+        out[c].y = R(0);
+        bet[c].x = R(0);
+        bet[c].y = R(0);
+      }
+      if (ok) {
+        const double4 g = p.src_geo[sd.src_off + s0 + s];
+        // tau = u l + v m + w (n - 1), metres (eq. k_term): error-free in
+        // float64, a plain float64 evaluation for the float32 path
+        const PhaseArg<sizeof(R) == 8> tau(s_uvw[ai][0], s_uvw[ai][1], s_uvw[ai][2], g.x, g.y,
+                                           g.z);
+        double r2b = 0.0, dl = 0.0, dm = 0.0, rb = 0.0;
+        if (p.beam) {
+          dl = g.x - s_pnt[ai][0];
+          dm = g.y - s_pnt[ai][1];
+          r2b = sumsq_rn(dl, dm);
+          rb = sqrt(r2b);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          if (c < ncv) {
+            R k3;
+            antenna_term<R, WITH_BETA>(p, tau, r2b, rb, c0 + c, out[c], k3);
             if (WITH_BETA) {
-              const R k3 = static_cast<R>(p.bk3[c0 + c]) * tx;
               bet[c].x = k3 * static_cast<R>(dl);
               bet[c].y = k3 * static_cast<R>(dm);
             }
           }
-          out[c].x = e * cs;
-          out[c].y = -e * sn;
         }
       }
-    }
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      s_a[s * L::AST + ai * NC + c] = out[c];
-      if (WITH_BETA) s_beta[s * L::AST + ai * NC + c] = bet[c];
+      for (int c = 0; c < NC; ++c) {
+        s_a[s * L::AST + ai * NC + c] = out[c];
+        if (WITH_BETA) s_beta[s * L::AST + ai * NC + c] = bet[c];
+      }
     }
   }
   // per-source records: the NC Stokes rows of the block's channels, then the
@@ -615,7 +617,7 @@ __device__ inline SrcTile src_tile(const SetDesc &sd, int k, int ns, int npt, in
 // source loops): they fit that in LDS and were VALU-idle a quarter of the
 // time at two (c2: float64-residual forward 29.5 -> 27.5 ms, FP64 chi^2
 // 28.5 -> 27.6 ms).  The gradient mode's LDS allows two workgroups anyway.
-template <class R, int NBT, int NC, int NS, int MODE, bool TERMS>
+template <class R, int NBT, int NC, int NS, int MODE, bool TERMS, bool PL>
 __global__ __launch_bounds__(NBT, (NBT == 256 && NC == 2 && sizeof(R) == 8 &&
                                    MODE != MODE_GRAD) ? 3 : 1)
 void rime_main(const KParams p) {
@@ -895,7 +897,7 @@ void rime_main(const KParams p) {
         const SrcTile st = src_tile(sd, k, NS, npt, ngt);
         const int cnt = st.cnt;
         __syncthreads();
-        stage_tile<R, NBT, NC, NS, MODE, false, TERMS>(p, sd, t, tile, st.s0, cnt,
+        stage_tile<R, NBT, NC, NS, MODE, false, TERMS, PL>(p, sd, t, tile, st.s0, cnt,
                                                 st.shape != SHAPE_POINT, c0, ncv, s_uvw, s_pnt,
                                                 s_a, s_beta, s_src);
         __syncthreads();
@@ -1014,7 +1016,7 @@ void rime_main(const KParams p) {
         const bool shaped = tl.shape != SHAPE_POINT;
         const bool disk = tl.shape == SHAPE_DISK;
         __syncthreads();
-        stage_tile<R, NBT, NC, NS, MODE, true, TERMS>(p, sd, t, tile, s0, cnt, shaped, c0, ncv,
+        stage_tile<R, NBT, NC, NS, MODE, true, TERMS, false>(p, sd, t, tile, s0, cnt, shaped, c0, ncv,
                                                       s_uvw, s_pnt, s_a, s_beta, s_src);
         __syncthreads();
         R gl[10];
@@ -1403,15 +1405,29 @@ hipError_t launch_sum_chunks(const double *part, int nchunk, int64_t stride, int
 // Launchers
 // ---------------------------------------------------------------------------
 
-// The instantiation with per-call terms runs only when a call has them.
+// The instantiation with per-call terms runs only when a call has them, and
+// the one that stages from planes (PL) when the call's extended sources have
+// planes (the forward modes of the float32 256-thread kernel).
 template <class R, int NBT, int NC, int NS, int MODE>
 static hipError_t launch_main(const KParams &p, int nitems, hipStream_t stream) {
-  if (p.die || p.stokes_t)
-    hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, true>), dim3(nitems), dim3(NBT), 0,
-                       stream, p);
+  const dim3 grid(nitems), block(NBT);
+  const bool terms = p.die || p.stokes_t;
+  if constexpr (sizeof(R) == 4 && NBT == 256 && NC == 2 &&
+                (MODE == MODE_PREDICT || MODE == MODE_CHI2)) {
+    if (p.pl_a) {
+      if (terms)
+        hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, true, true>), grid, block, 0, stream,
+                           p);
+      else
+        hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, false, true>), grid, block, 0, stream,
+                           p);
+      return hipGetLastError();
+    }
+  }
+  if (terms)
+    hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, true, false>), grid, block, 0, stream, p);
   else
-    hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, false>), dim3(nitems), dim3(NBT), 0,
-                       stream, p);
+    hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, false, false>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 
