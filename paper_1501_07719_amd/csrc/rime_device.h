@@ -47,6 +47,15 @@ __device__ inline uint32_t opaque_vgpr(uint32_t x) {
   return x;
 }
 
+// A float64 constant in an SGPR pair: an operand of v_fma_f64, where hipcc
+// otherwise copies the constant into the destination of a v_fmac_f64 each time.
+__device__ inline double sgpr_const(double x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+s"(x));
+#endif
+  return x;
+}
+
 // The set descriptor of a work item, read through the constant space so that
 // its fields are wavefront-uniform (scalar) values.
 __device__ inline SetDesc load_set(const KParams &p, int set) {
@@ -74,10 +83,31 @@ template <> struct Num<double> {
   __device__ static inline void sincos_turns(double r, double *s, double *c) {
     sincospi(2.0 * r, s, c);
   }
-  // expb(y) = exp(y / kExpScale): the exponential in the base whose argument
-  // scale is kExpScale (e here, 2 in the float version).
-  static constexpr double kExpScale = 1.0;
-  __device__ static inline double expb(double y) { return exp(y); }
+  // expb(y) = exp(y / kExpScale) = 2^y for y <= 0.  2^y = 2^n 2^f with n the
+  // nearest integer and f = y - n exact; 2^f on [-1/2, 1/2] is the polynomial
+  // that interpolates it at the 12 Chebyshev nodes, 2.0e-17 relative with the
+  // coefficients rounded to float64.  19 instructions against 24 of exp().
+  // Below 2^-1100 the result is 0 (the cut keeps y = -infinity finite; a NaN
+  // passes through).
+  static constexpr double kExpScale = kLog2e;
+  __device__ static inline double expb(double y) {
+    y = y < -1100.0 ? -1100.0 : y;
+    const double n = rint(y);
+    const double f = y - n;
+    double r = sgpr_const(4.4558179083360645e-10);
+    r = fma(r, f, sgpr_const(7.074194297288521e-09));
+    r = fma(r, f, sgpr_const(1.0178057087733941e-07));
+    r = fma(r, f, sgpr_const(1.3215432535912375e-06));
+    r = fma(r, f, sgpr_const(1.5252733841556773e-05));
+    r = fma(r, f, sgpr_const(0.00015403530463724353));
+    r = fma(r, f, sgpr_const(0.001333355814640647));
+    r = fma(r, f, sgpr_const(0.009618129107587256));
+    r = fma(r, f, sgpr_const(0.055504108664821625));
+    r = fma(r, f, sgpr_const(0.24022650695910158));
+    r = fma(r, f, sgpr_const(0.6931471805599453));
+    r = fma(r, f, 1.0);
+    return __builtin_amdgcn_ldexp(r, static_cast<int>(n));
+  }
   // the 32 bits packed into the last word of a per-baseline record
   __device__ static inline uint32_t bits(double w) {
     return static_cast<uint32_t>(__double_as_longlong(w));
@@ -234,6 +264,32 @@ __device__ inline double sumsq_rn(double a, double b) {
   return a * a + b * b;
 }
 
+// Kernel modes.  MODE_RESID is the forward of the float64-residual mixed
+// mode: float64 arithmetic over float32 data and weights, chi^2 partials and,
+// when p.rho_b is set, the weighted residual in Stokes form (float32) per
+// visibility and, with p.pme_adj, in the antenna-pair slots.  MODE_ADJ is its
+// float32 adjoint: pass 2 alone, over the residual read from p.rho_b.
+enum { MODE_PREDICT = 0, MODE_CHI2 = 1, MODE_GRAD = 2, MODE_RESID = 3, MODE_ADJ = 4 };
+
+template <bool B, class X, class Y> struct Pick { using T = X; };
+template <class X, class Y> struct Pick<false, X, Y> { using T = Y; };
+
+// Source tiles of a set: points first, then Gaussians, then disks; tile k
+// covers sources [s0, s0 + cnt) of one morphology.
+struct SrcTile {
+  int shape, s0, cnt;
+};
+
+__device__ inline SrcTile src_tile(const SetDesc &sd, int k, int ns, int npt, int ngt) {
+  if (k < npt) return {SHAPE_POINT, k * ns, min(ns, sd.npsrc - k * ns)};
+  if (k < npt + ngt) {
+    const int s0 = sd.npsrc + (k - npt) * ns;
+    return {SHAPE_GAUSS, s0, min(ns, sd.npsrc + sd.ngsrc - s0)};
+  }
+  const int s0 = sd.npsrc + sd.ngsrc + (k - npt - ngt) * ns;
+  return {SHAPE_DISK, s0, min(ns, sd.npsrc + sd.ngsrc + sd.nxsrc - s0)};
+}
+
 // The per-antenna term of one (antenna, source) at channel c: a = e K and, for
 // the adjoint, k3 with d ln e / d(l, m) = k3 (l - dl_p, m - dm_p).  The angles
 // are formed in float64 and their sines and cosines to within about a unit of
@@ -321,38 +377,6 @@ __device__ inline Comp block_reduce(Comp v, double2 *scratch) {
   return r;
 }
 
-// Workgroups are dealt round-robin to the 8 XCDs; renumbering them makes
-// consecutive work items (which share operands through L2) land on one XCD.
-__device__ inline int xcd_item(int nitems) {
-  const int per_xcd = (nitems + 7) / 8;
-  return static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
-}
-
-// St'_k (k = I, Q, U, V) of source s of the set at channel c and timestep t:
-// the spectrally scaled Stokes vector, or, with brightness per timestep (ST),
-// the spectral factor times that timestep's Stokes vector (rounded as in the
-// per-baseline kernels).  The kernels that call it per chunk take ST as a
-// template parameter, so that the plain calls do not carry its registers.
-template <bool ST, class R>
-__device__ inline typename Num<R>::R4 pme_stokes(const KParams &p, int s, int c, int t) {
-  using R4 = typename Num<R>::R4;
-  const int64_t gs = p.one.src_off + s;
-  if (ST) {
-    const int nsrc = p.one.npsrc + p.one.ngsrc + p.one.nxsrc;
-    const double *q = p.stokes_t + (static_cast<int64_t>(t) * nsrc + s) * 4;
-    const double f = static_cast<double>(static_cast<const R *>(p.src_sf)[gs * p.nchan + c]);
-    R4 v;
-    v.x = static_cast<R>(f * q[0]);
-    v.y = static_cast<R>(f * q[1]);
-    v.z = static_cast<R>(f * q[2]);
-    v.w = static_cast<R>(f * q[3]);
-    return v;
-  }
-  return static_cast<const R4 *>(p.src_st)[gs * p.nchan + c];
-}
-
-constexpr int nat_for(int nbt) { return nbt >= 1024 ? 64 : nbt >= 256 ? 32 : 16; }
-
 // 2x2 complex matrices in float64, entries (xx, xy, yx, yy) = ([0][0], [0][1],
 // [1][0], [1][1]).
 struct M22 {
@@ -402,5 +426,151 @@ __device__ inline M22 m22_load(const double2 *m) {
   }
   return r;
 }
+
+// V of one visibility from its Stokes sums S (re, im of I, Q, U, V), and, in
+// the chi^2 modes, its weighted squared residual (added to `chi`) and, with
+// RHO, the weighted residual in Stokes form `rho` that the adjoint takes.
+//   PREDICT: V goes to p.vis.  DT: type of data and weights (and of vis).
+//   gap, gaq: the baseline's antennas; gg: its diagonal gain products
+//   g_pi conj(g_qj); c: channel (with !ok any valid one; nothing is then read
+//   or written and rho = 0); vidx: index of the visibility's first correlation.
+template <class R, class DT, class A, bool PREDICT, bool RHO, bool TERMS>
+__device__ inline void visibility(const KParams &p, bool ok, int t, int gap, int gaq, int c,
+                                  int64_t vidx, const double (&S)[8], const double2 (&gg)[4],
+                                  Comp &chi, typename Num<A>::R2 (&rho)[4]) {
+  using R2 = typename Num<R>::R2;
+  using DT2 = typename Num<DT>::R2;
+  // Stokes sums -> 2x2 coherency X (eq. brightness_term)
+  const double SIr = S[0], SIi = S[1], SQr = S[2], SQi = S[3];
+  const double SUr = S[4], SUi = S[5], SVr = S[6], SVi = S[7];
+  M22 X;
+  X.re[0] = SIr + SQr;  // xx
+  X.im[0] = SIi + SQi;
+  X.re[1] = SUr - SVi;  // xy = S_U + i S_V
+  X.im[1] = SUi + SVr;
+  X.re[2] = SUr + SVi;  // yx = S_U - i S_V
+  X.im[2] = SUi - SVr;
+  X.re[3] = SIr - SQr;  // yy
+  X.im[3] = SIi - SQi;
+  double Vr[4], Vi[4];
+  // V = G_p X G_q^H (eq. 1's direction-independent term, outside the
+  // source sum), or the plan's diagonal gains
+  M22 Gp, Gq;
+  if (TERMS && p.die) {
+    const int64_t gi = (static_cast<int64_t>(t) * p.na) * p.nchan + c;
+    Gp = m22_load(p.die + (gi + static_cast<int64_t>(gap) * p.nchan) * 4);
+    Gq = m22_load(p.die + (gi + static_cast<int64_t>(gaq) * p.nchan) * 4);
+    const M22 V = m22_mul(m22_mul(Gp, X), m22_herm(Gq));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      Vr[k] = V.re[k];
+      Vi[k] = V.im[k];
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      Vr[k] = X.re[k] * gg[k].x - X.im[k] * gg[k].y;
+      Vi[k] = X.re[k] * gg[k].y + X.im[k] * gg[k].x;
+    }
+  }
+  if (PREDICT) {
+    if (ok) {
+      R2 *out = static_cast<R2 *>(p.vis) + vidx;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        R2 v;
+        v.x = static_cast<R>(Vr[k]);
+        v.y = static_cast<R>(Vi[k]);
+        out[k] = v;
+      }
+    }
+    return;
+  }
+  double Yr[4] = {0, 0, 0, 0}, Yi[4] = {0, 0, 0, 0};
+  if (ok) {
+    const DT2 *D = static_cast<const DT2 *>(p.data) + vidx;
+    const DT *W = static_cast<const DT *>(p.weight) + vidx;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const DT2 d = D[k];
+      const double w = static_cast<double>(W[k]);
+      const double rr = Vr[k] - static_cast<double>(d.x);
+      const double ri = Vi[k] - static_cast<double>(d.y);
+      chi.add(w * (rr * rr + ri * ri));
+      Yr[k] = w * rr;
+      Yi[k] = w * ri;
+    }
+  }
+  if (!RHO) return;
+  // the residual carried to the coherency X: Z = G_p^H Y G_q (with
+  // diagonal gains Z_ij = Y_ij conj(g_pi) g_qj = Y_ij conj(gg_ij)); then
+  // rho_I = conj(Zxx) + conj(Zyy), rho_Q = conj(Zxx) - conj(Zyy),
+  // rho_U = conj(Zxy) + conj(Zyx), rho_V = i (conj(Zxy) - conj(Zyx))
+  double Zr[4], Zi[4];
+  if (TERMS && p.die) {
+    M22 Y;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      Y.re[k] = Yr[k];
+      Y.im[k] = Yi[k];
+    }
+    const M22 Z = m22_mul(m22_mul(m22_herm(Gp), Y), Gq);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      Zr[k] = Z.re[k];
+      Zi[k] = Z.im[k];
+    }
+    if (ok && p.die_part) {
+      // d chi^2 / d conj(G) of this visibility: Y G_q X^H for antenna
+      // p and Y^H G_p X for antenna q
+      const M22 Ap = m22_mul(m22_mul(Y, Gq), m22_herm(X));
+      const M22 Aq = m22_mul(m22_mul(m22_herm(Y), Gp), X);
+      double2 *dp = p.die_part + vidx * 2;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        dp[k] = make_double2(Ap.re[k], Ap.im[k]);
+        dp[4 + k] = make_double2(Aq.re[k], Aq.im[k]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      Zr[k] = Yr[k] * gg[k].x + Yi[k] * gg[k].y;
+      Zi[k] = Yi[k] * gg[k].x - Yr[k] * gg[k].y;
+    }
+  }
+  rho[0].x = static_cast<A>(Zr[0] + Zr[3]);
+  rho[0].y = static_cast<A>(-(Zi[0] + Zi[3]));
+  rho[1].x = static_cast<A>(Zr[0] - Zr[3]);
+  rho[1].y = static_cast<A>(-(Zi[0] - Zi[3]));
+  rho[2].x = static_cast<A>(Zr[1] + Zr[2]);
+  rho[2].y = static_cast<A>(-(Zi[1] + Zi[2]));
+  rho[3].x = static_cast<A>(Zi[1] - Zi[2]);
+  rho[3].y = static_cast<A>(Zr[1] - Zr[2]);
+}
+
+// The plan's diagonal gain products of baseline (gap, gaq): g_pi conj(g_qj).
+__device__ inline void gain_products(const KParams &p, int gap, int gaq, double2 (&gg)[4]) {
+  const double2 gpi[2] = {make_double2(p.gains[4 * gap + 0], p.gains[4 * gap + 1]),
+                          make_double2(p.gains[4 * gap + 2], p.gains[4 * gap + 3])};
+  const double2 gqj[2] = {make_double2(p.gains[4 * gaq + 0], p.gains[4 * gaq + 1]),
+                          make_double2(p.gains[4 * gaq + 2], p.gains[4 * gaq + 3])};
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const double2 a = gpi[i], b = gqj[j];
+      gg[2 * i + j] = make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+    }
+}
+
+// Workgroups are dealt round-robin to the 8 XCDs; renumbering them makes
+// consecutive work items (which share operands through L2) land on one XCD.
+__device__ inline int xcd_item(int nitems) {
+  const int per_xcd = (nitems + 7) / 8;
+  return static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
+}
+
+constexpr int nat_for(int nbt) { return nbt >= 1024 ? 64 : nbt >= 256 ? 32 : 16; }
 
 }  // namespace rime

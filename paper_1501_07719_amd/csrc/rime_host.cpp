@@ -25,6 +25,10 @@ hipError_t launch_pme_adjoint(const KParams &p, bool phase, hipStream_t stream);
 hipError_t launch_pme_finalize(const KParams &p, hipStream_t stream);
 hipError_t launch_pme_scale(const KParams &p, hipStream_t stream);
 hipError_t launch_planes(const KParams &p, hipStream_t stream);
+hipError_t launch_p64_planes(const KParams &p, hipStream_t stream);
+hipError_t launch_p64_forward(const KParams &p, int mode, hipStream_t stream);
+hipError_t launch_p64_adjoint(const KParams &p, hipStream_t stream);
+hipError_t launch_p64_finalize(const KParams &p, hipStream_t stream);
 int variant_count(int mode, int prec);
 const Variant *variant_info(int mode, int prec, int index);
 hipError_t launch_variant(int mode, int prec, int index, const KParams &p, int nitems,
@@ -105,6 +109,11 @@ struct rime_plan {
   int32_t ngroup = 0;
   int32_t pme_pairs = 0;        // forward groups pair two P blocks
   int32_t *d_groups = nullptr;  // [ngroup][5] forward work groups
+  // float64 engine: 16 x 16 antenna sub-blocks that hold baselines, the
+  // baseline of every antenna-pair slot, and the forward's wavefront tasks
+  // with four baselines and with one baseline per lane
+  int32_t nsub = 0, ntask4 = 0, ntask1 = 0;
+  int32_t *d_sub = nullptr, *d_slot_bl = nullptr, *d_task4 = nullptr, *d_task1 = nullptr;
   bool pme_adj_ok = false;  // every antenna-pair slot holds at most one baseline
   int32_t *d_ant_off = nullptr;  // [na + 1] baselines of each antenna (both sides)
   int2 *d_ant_bl = nullptr;      // [2 nbl] (baseline, 0: p / 1: q)
@@ -315,6 +324,8 @@ struct WsLayout {
   size_t dom = 0;
   size_t die_part = 0, src_sf = 0, gst = 0;
   size_t geo = 0, lon = 0, st = 0, gs = 0, rec = 0, chi2 = 0, grad = 0, grad2 = 0;
+  size_t p64_a = 0, p64_k3 = 0, p64_geo = 0, p64_rho = 0, p64_part = 0;
+  bool p64 = false;        // the float64 engine runs this call
   size_t ph_hi = 0, spts = 0, pexp = 0, rho_t = 0, pgrad = 0;
   size_t src_f = 0, mfrag = 0, mscale = 0, rho_g = 0, pfin = 0;
   int32_t pme_tchunk = 0;  // timesteps per phase-plane pass (0: engine off)
@@ -343,6 +354,88 @@ bool pme_active(const Variant &v, int prec, int nset) {
   return v.pme && prec != RIME_FP64 && nset == 1;
 }
 
+// The float64 engine (rime_p64.hip) runs the float64 forward and gradient of
+// single-sky calls with the default variant's shape (256 threads, two
+// channels per thread) on arrays of more than 96 baselines, none of them twice
+// (an antenna-pair slot holds one), for skies of 32 sources and more: below, a
+// launch more costs what the shorter loops save (46 antennas, 4 (timestep,
+// channel), predict: 40 sources 17.4 against 21.4 us, 8 sources 14.3 against
+// 12.1).  The other calls, and calls whose workspace does not hold its planes,
+// run on the per-baseline kernel.
+bool p64_active(const rime_plan *plan, const Variant &v, int prec, int nset, int64_t total_src) {
+  return prec == RIME_FP64 && nset == 1 && v.threads == 256 && v.nc == 2 &&
+         plan->nbl > 96 && plan->pme_adj_ok && total_src >= 32;
+}
+
+// Whether a call on such a plan takes the engine for its sky: a gradient only
+// when at least half of the lanes of its groups of 64 sources of one
+// morphology hold a source (46 antennas, 1600 (timestep, channel), 28 points +
+// 23 Gaussians: 744 us against 716 us on the per-baseline kernel).
+bool p64_takes(int mode, const SetDesc &d) {
+  if (mode != RIME_MODE_CHI2_GRAD) return true;
+  const int n = d.npsrc + d.ngsrc + d.nxsrc;
+  const int groups = (d.npsrc + kWave - 1) / kWave + (d.ngsrc + kWave - 1) / kWave +
+                     (d.nxsrc + kWave - 1) / kWave;
+  return 2 * n >= groups * kWave;
+}
+
+// Upper bound on the planes and residual slots of one time pass of the engine.
+constexpr size_t kP64PassBytes = size_t(24) << 30;
+
+struct P64Geometry {
+  int nap = 0, ns = 0;     // padded antennas and sources of the planes
+  bool k3 = false;         // planes of the beam-gradient factor
+  size_t plane_t = 0;      // plane entries per timestep
+  size_t rho_t = 0;        // residual slots x 4 per timestep
+  int tpass = 1;           // timesteps per pass
+  int nr = 4, ntask = 0;   // forward: baselines per lane, tasks
+  int tch = 1;             // forward: timesteps per work item
+  int64_t nitem = 0;       // forward work items of the call
+  int ncw = 1, ncg = 1;    // adjoint: channels per work item, channel groups
+  int64_t nsg_max = 0;     // bound on its groups of 64 sources
+  int split = 1;           // parts of a sub-block per work item
+};
+
+P64Geometry p64_geometry(const rime_plan *plan, int mode, int64_t total_src) {
+  P64Geometry g;
+  const bool grad = mode == RIME_MODE_CHI2_GRAD;
+  g.nap = (plan->na + 15) / 16 * 16;
+  g.k3 = grad && plan->beam;
+  g.ns = static_cast<int>((total_src + 7) / 8 * 8);
+  g.plane_t = static_cast<size_t>(plan->nchan) * g.ns * g.nap;
+  g.rho_t = grad ? static_cast<size_t>(plan->nchan) * plan->npair * kPmeBlk * kPmeBlk * 4 : 0;
+  const size_t per_t = g.plane_t * (sizeof(double2) + (g.k3 ? sizeof(double) : 0)) +
+                       g.rho_t * sizeof(double2);
+  g.tpass = static_cast<int>(
+      std::max<size_t>(1, std::min<size_t>(plan->ntime, kP64PassBytes / per_t)));
+  // four baselines per lane once that gives the chip's 1024 SIMDs two
+  // wavefronts each; one per lane below (shorter chains on an idle chip)
+  const int64_t w4 = static_cast<int64_t>(plan->ntime) * plan->nchan * plan->ntask4;
+  g.nr = w4 >= 2048 ? 4 : 1;
+  g.ntask = g.nr == 4 ? plan->ntask4 : plan->ntask1;
+  const int64_t per = static_cast<int64_t>(plan->nchan) * g.ntask;  // items per time chunk
+  g.tch = static_cast<int>(std::max<int64_t>(
+      1, std::min<int64_t>(g.tpass, (per * plan->ntime + 32767) / 32768)));
+  int64_t nch = 0;
+  for (int t0 = 0; t0 < plan->ntime; t0 += g.tpass)
+    nch += (std::min(g.tpass, plan->ntime - t0) + g.tch - 1) / g.tch;
+  g.nitem = nch * per;
+  g.nsg_max = total_src / kWave + 3;
+  const int64_t one = g.nsg_max * plan->ntime * plan->nsub;  // items with one channel group
+  const int64_t ncw = std::max<int64_t>(1, std::min<int64_t>(plan->nchan,
+                                                             one * plan->nchan / 65536));
+  g.ncg = static_cast<int>((plan->nchan + ncw - 1) / ncw);
+  g.ncw = (plan->nchan + g.ncg - 1) / g.ncg;
+  g.ncg = (plan->nchan + g.ncw - 1) / g.ncw;
+  // one wavefront's sub-block takes tens of microseconds; eighths of it while
+  // that leaves the chip's 2048 resident wavefronts unfilled
+  g.split = g.nsg_max * plan->ntime * g.ncg * plan->nsub < 4096 ? 8 : 1;
+  return g;
+}
+
+// Chunks of adjoint items that the first pass of the engine's gradient sums forms.
+constexpr int kP64FinChunks = 64;
+
 // Words of the domain-flag header at the start of every workspace: a count,
 // then one flag per (set, preparation workgroup of 256 sources).
 int64_t dom_words(int nset, int64_t total_src) {
@@ -350,10 +443,15 @@ int64_t dom_words(int nset, int64_t total_src) {
 }
 
 // fwd_sums = false: the point-source sums of the matrix-core forward are not
-// needed (the adjoint half of the float64-residual mode).
+// needed (the adjoint half of the float64-residual mode).  lean: the least that
+// the call can run with (without the float64 engine).
 WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g, int nset,
-                   int64_t total_src, const Variant &v, bool fwd_sums = true, int terms = 0) {
+                   int64_t total_src, const Variant &v, bool fwd_sums = true, int terms = 0,
+                   bool lean = false) {
   WsLayout L;
+  L.p64 = !lean && p64_active(plan, v, prec, nset, total_src);
+  const P64Geometry pg = L.p64 ? p64_geometry(plan, mode, total_src) : P64Geometry{};
+  const bool base = !L.p64;  // regions of the per-baseline kernel
   const size_t r4 = prec == RIME_FP64 ? 32 : 16;
   size_t off = 0;
   L.dom = off;
@@ -362,25 +460,28 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
   off += align_up(static_cast<size_t>(total_src) * sizeof(double4));
   L.lon = off;
   off += align_up(static_cast<size_t>(total_src) * sizeof(double2));
+  const size_t rows = L.p64 ? pg.ns : total_src;
   L.st = off;
-  off += align_up(static_cast<size_t>(total_src) * plan->nchan * r4);
+  off += align_up(rows * plan->nchan * r4);
   L.gs = off;
   off += align_up(static_cast<size_t>(total_src) * r4);
-  if (mode == RIME_MODE_CHI2_GRAD) {
+  if (base && mode == RIME_MODE_CHI2_GRAD) {
     L.rec = off;
     off += align_up((static_cast<size_t>(plan->ntime) * g.ntile * v.threads + kRecPad) * r4);
   }
   L.chi2 = off;
   if (mode != RIME_MODE_PREDICT)
-    off += align_up(static_cast<size_t>(nset) * g.items_per_set * sizeof(double2));
+    off += align_up((L.p64 ? static_cast<size_t>(pg.nitem)
+                           : static_cast<size_t>(nset) * g.items_per_set) *
+                    sizeof(double2));
   L.grad = off;
-  if (mode == RIME_MODE_CHI2_GRAD)
+  if (base && mode == RIME_MODE_CHI2_GRAD)
     off += align_up(static_cast<size_t>(g.items_per_set) * total_src * 10 * sizeof(double));
   L.grad2 = off;
-  if (mode == RIME_MODE_CHI2_GRAD)
+  if (base && mode == RIME_MODE_CHI2_GRAD)
     off += align_up(static_cast<size_t>(g.grad_nchunk) * total_src * 10 * sizeof(double2));
   L.rho_g = off;
-  if (mode == RIME_MODE_CHI2_GRAD && prec == RIME_FP64 && v.nc == 2 && v.threads >= 256)
+  if (base && mode == RIME_MODE_CHI2_GRAD && prec == RIME_FP64 && v.nc == 2 && v.threads >= 256)
     off += align_up(static_cast<size_t>(nset) * g.items_per_set * v.threads * v.nc * 4 *
                     sizeof(double2));
   // (a sky without sources leaves the engine off)
@@ -428,16 +529,38 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
       off += align_up(nfrag * sizeof(float));
     }
   }
+  if (L.p64) {
+    L.p64_a = off;
+    off += align_up(pg.plane_t * pg.tpass * sizeof(double2));
+    L.has_k3 = pg.k3;
+    if (pg.k3) {
+      L.p64_k3 = off;
+      off += align_up(pg.plane_t * pg.tpass * sizeof(double));
+    }
+    if (mode == RIME_MODE_CHI2_GRAD) {
+      L.p64_geo = off;
+      off += align_up(static_cast<size_t>(plan->ntime) * plan->npair * kPmeBlk * kPmeBlk *
+                      sizeof(double2));
+      L.p64_rho = off;
+      off += align_up(pg.rho_t * pg.tpass * sizeof(double2));
+      L.p64_part = off;
+      off += align_up(static_cast<size_t>(pg.nsg_max) * plan->ntime * pg.ncg * plan->nsub * pg.split * 10 *
+                      kWave * sizeof(double));
+      L.pfin = off;
+      off += align_up(static_cast<size_t>(pg.nsg_max) * kP64FinChunks * 10 * kWave *
+                      sizeof(double2));
+    }
+  }
   if (terms & TERM_DIE_GRAD) {
     L.die_part = off;
     off += align_up(static_cast<size_t>(plan->ntime) * plan->nbl * plan->nchan * 8 *
                     sizeof(double2));
   }
-  if (terms & TERM_STOKES_T) {
+  if ((terms & TERM_STOKES_T) || (L.p64 && mode == RIME_MODE_CHI2_GRAD)) {
     L.src_sf = off;
-    off += align_up(static_cast<size_t>(total_src) * plan->nchan * (r4 / 4));
+    off += align_up(rows * plan->nchan * (r4 / 4));
   }
-  if ((terms & TERM_STOKES_T_GRAD) && mode == RIME_MODE_CHI2_GRAD) {
+  if (base && (terms & TERM_STOKES_T_GRAD) && mode == RIME_MODE_CHI2_GRAD) {
     L.gst = off;
     off += align_up(static_cast<size_t>(g.items_per_set) * g.tchunk * total_src * 4 *
                     sizeof(double));
@@ -456,12 +579,13 @@ struct Res64Layout {
 };
 
 Res64Layout res64_layout(const rime_plan *plan, int mode, const Variant &vf,
-                         const Variant *va, int nset, int64_t total_src, int terms = 0) {
+                         const Variant *va, int nset, int64_t total_src, int terms = 0,
+                         bool lean = false) {
   Res64Layout R;
   // the forward writes the partials of the G gradient; both halves stage the
   // brightness per timestep; the adjoint writes its per-timestep partials
   R.f = ws_layout(plan, RIME_MODE_CHI2, RIME_FP64, geometry(plan, vf, nset), nset, total_src,
-                  vf, true, terms & (TERM_DIE_GRAD | TERM_STOKES_T));
+                  vf, true, terms & (TERM_DIE_GRAD | TERM_STOKES_T), lean);
   size_t off = R.f.total;
   if (mode == RIME_MODE_CHI2_GRAD && va) {
     R.va = *va;
@@ -480,19 +604,24 @@ Res64Layout res64_layout(const rime_plan *plan, int mode, const Variant &vf,
 }
 
 // Workspace of one call of (mode, prec) with kernel variant `vidx` and, for a
-// gradient in the float64-residual mode, forward variant `fidx`.
+// gradient in the float64-residual mode, forward variant `fidx`; lean: the
+// least that the call accepts.
 size_t call_ws(const rime_plan *plan, int mode, int prec, int vidx, int fidx, int nset,
-               int64_t total_src, int terms = 0) {
+               int64_t total_src, int terms = 0, bool lean = false) {
+  size_t best = 0;
   const Variant *v = variant_info(mode, prec, vidx);
   if (!v) return 0;
+  if (!lean)  // a call may also run without the engine, whatever its sky
+    best = call_ws(plan, mode, prec, vidx, fidx, nset, total_src, terms, true);
   if (prec != kRes64)
-    return ws_layout(plan, mode, prec, geometry(plan, *v, nset), nset, total_src, *v, true, terms)
-        .total;
+    return std::max(best, ws_layout(plan, mode, prec, geometry(plan, *v, nset), nset, total_src, *v,
+                                    true, terms, lean)
+                              .total);
   if (mode == RIME_MODE_CHI2)
-    return res64_layout(plan, mode, *v, nullptr, nset, total_src, terms).total;
+    return std::max(best, res64_layout(plan, mode, *v, nullptr, nset, total_src, terms, lean).total);
   const Variant *vf = variant_info(RIME_MODE_CHI2, kRes64, fidx);
   if (!vf) return 0;
-  return res64_layout(plan, mode, *vf, v, nset, total_src, terms).total;
+  return std::max(best, res64_layout(plan, mode, *vf, v, nset, total_src, terms, lean).total);
 }
 
 // Whether a batched call with this variant runs the single-sky pipeline once
@@ -508,7 +637,8 @@ bool per_set_variant(const rime_plan *plan, int mode, int prec, const Variant &v
 // most of the chip idle).
 constexpr int kBatchLanes = 2;
 
-size_t ws_max(const rime_plan *plan, int mode, int prec, int nset, int64_t total_src) {
+size_t ws_max(const rime_plan *plan, int mode, int prec, int nset, int64_t total_src,
+              bool lean = false) {
   size_t best = 0;
   const int nf = prec == kRes64 && mode == RIME_MODE_CHI2_GRAD
                      ? variant_count(RIME_MODE_CHI2, kRes64)
@@ -516,7 +646,7 @@ size_t ws_max(const rime_plan *plan, int mode, int prec, int nset, int64_t total
   for (int i = 0; i < variant_count(mode, prec); ++i) {
     const Variant *v = variant_info(mode, prec, i);
     for (int f = 0; f < nf; ++f) {
-      best = std::max(best, call_ws(plan, mode, prec, i, f, nset, total_src));
+      best = std::max(best, call_ws(plan, mode, prec, i, f, nset, total_src, 0, lean));
       // a batched call with a matrix-core variant runs one set at a time in
       // up to kBatchLanes lanes after a header of domain flags; no set has
       // more than total_src sources
@@ -524,7 +654,7 @@ size_t ws_max(const rime_plan *plan, int mode, int prec, int nset, int64_t total
         best = std::max(best, align_up(static_cast<size_t>(dom_words(nset, total_src)) *
                                        sizeof(int32_t)) +
                                   std::min(kBatchLanes, nset) *
-                                      align_up(call_ws(plan, mode, prec, i, f, 1, total_src)));
+                                      align_up(call_ws(plan, mode, prec, i, f, 1, total_src, 0, lean)));
     }
   }
   return best;
@@ -705,7 +835,38 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
   p.stokes_t = c.stokes_t;
   if (c.stokes_t) p.src_sf = w + L.src_sf;
   p.grad_stokes_t = c.grad_stokes_t;
-  if (c.grad_stokes_t && c.mode == RIME_MODE_CHI2_GRAD)
+  if (L.p64) {
+    const P64Geometry pg = p64_geometry(plan, c.mode, c.total_src);
+    p.nap = pg.nap;
+    p.p64_ns = pg.ns;
+    p.npair = plan->npair;
+    p.pair_blk = plan->d_pair_blk;
+    p.pair_mask = plan->d_pair_mask;
+    p.slot_bl = plan->d_slot_bl;
+    p.p64_a = reinterpret_cast<double2 *>(w + L.p64_a);
+    p.p64_nr = pg.nr;
+    p.p64_ntask = pg.ntask;
+    p.p64_task = pg.nr == 4 ? plan->d_task4 : plan->d_task1;
+    p.p64_tch = pg.tch;
+    p.items_per_set = static_cast<int32_t>(pg.nitem);
+    if (c.mode == RIME_MODE_CHI2_GRAD) {
+      if (L.has_k3) p.p64_k3 = reinterpret_cast<double *>(w + L.p64_k3);
+      p.p64_geo = reinterpret_cast<double2 *>(w + L.p64_geo);
+      p.p64_rho = reinterpret_cast<double2 *>(w + L.p64_rho);
+      p.p64_part = reinterpret_cast<double *>(w + L.p64_part);
+      p.pfin = reinterpret_cast<double2 *>(w + L.pfin);
+      p.src_sf = w + L.src_sf;
+      p.nsub = plan->nsub;
+      p.sub = plan->d_sub;
+      p.p64_ncw = pg.ncw;
+      p.p64_ncg = pg.ncg;
+      p.p64_nsg = (c.one.npsrc + kWave - 1) / kWave + (c.one.ngsrc + kWave - 1) / kWave +
+                  (c.one.nxsrc + kWave - 1) / kWave;
+      p.pme_fchunk = static_cast<int>(std::min<int64_t>(
+          kP64FinChunks, static_cast<int64_t>(plan->ntime) * pg.ncg * plan->nsub * pg.split));
+      p.p64_split = pg.split;
+    }
+  } else if (c.grad_stokes_t && c.mode == RIME_MODE_CHI2_GRAD)
     p.gst_part = reinterpret_cast<double *>(w + L.gst);
   p.pme = 0;
   p.pme_adj = 0;
@@ -744,6 +905,23 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
   return p;
 }
 
+// The float64 engine's kernels, in passes over time: planes, forward (kernel
+// mode `fmode`: the call's mode, or 3 for the float64-residual forward) and,
+// for a gradient, the adjoint.
+rime_status enqueue_p64(const rime_plan *plan, KParams p, int mode, int fmode, int64_t total_src,
+                        hipStream_t stream) {
+  const P64Geometry pg = p64_geometry(plan, mode, total_src);
+  for (int t0 = 0; t0 < plan->ntime; t0 += pg.tpass) {
+    p.pme_t0 = t0;
+    p.pme_nt = std::min(pg.tpass, plan->ntime - t0);
+    RIME_HIP(launch_p64_planes(p, stream));
+    RIME_HIP(launch_p64_forward(p, fmode, stream));
+    if (mode == RIME_MODE_CHI2_GRAD) RIME_HIP(launch_p64_adjoint(p, stream));
+    p.p64_item0 += static_cast<int64_t>((p.pme_nt + pg.tch - 1) / pg.tch) * plan->nchan * pg.ntask;
+  }
+  return RIME_OK;
+}
+
 // The point-source adjoint on the matrix cores, in passes over time that
 // each rebuild their phase planes unless `reuse` (one pass whose planes the
 // forward left in place).
@@ -767,7 +945,9 @@ rime_status enqueue_res64(const rime_plan *plan, const Call &c, int vidx, void *
   const Variant *vf = variant_info(RIME_MODE_CHI2, kRes64, fidx);
   const Variant *va = grad ? variant_info(RIME_MODE_CHI2_GRAD, kRes64, vidx) : nullptr;
   if (!vf || (grad && !va)) return RIME_ERR_UNSUPPORTED;
-  const Res64Layout R = res64_layout(plan, c.mode, *vf, va, c.nset, c.total_src, c.terms());
+  Res64Layout R = res64_layout(plan, c.mode, *vf, va, c.nset, c.total_src, c.terms());
+  if (ws_bytes < R.total)
+    R = res64_layout(plan, c.mode, *vf, va, c.nset, c.total_src, c.terms(), true);
   if (!ws || ws_bytes < R.total) return RIME_ERR_WORKSPACE;
   const Geometry gf = geometry(plan, *vf, c.nset);
   const Geometry ga = grad ? geometry(plan, R.va, c.nset) : Geometry{};
@@ -803,7 +983,12 @@ rime_status enqueue_res64(const rime_plan *plan, const Call &c, int vidx, void *
   if (grad) RIME_HIP(launch_prep(pa, false, c.max_nsrc, R.va.nc, stream));
   if (events && plan->ev_start) RIME_HIP(hipEventRecord(plan->ev_start, stream));
   if (events && plan->ev_main0) RIME_HIP(hipEventRecord(plan->ev_main0, stream));
-  RIME_HIP(launch_resid(fidx, pf, static_cast<int>(nf), stream));
+  if (R.f.p64) {
+    const rime_status st = enqueue_p64(plan, pf, RIME_MODE_CHI2, 3, c.total_src, stream);
+    if (st != RIME_OK) return st;
+  } else {
+    RIME_HIP(launch_resid(fidx, pf, static_cast<int>(nf), stream));
+  }
   if (events && plan->ev_main1) RIME_HIP(hipEventRecord(plan->ev_main1, stream));
   if (grad) {
     if (pa.pme_adj) {
@@ -831,7 +1016,9 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
   const Variant *v = variant_info(mode, prec, vidx);
   if (!v) return RIME_ERR_UNSUPPORTED;
   const Geometry g = geometry(plan, *v, c.nset);
-  const WsLayout L = ws_layout(plan, mode, prec, g, c.nset, c.total_src, *v, true, c.terms());
+  WsLayout L = ws_layout(plan, mode, prec, g, c.nset, c.total_src, *v, true, c.terms());
+  if (ws_bytes < L.total || (L.p64 && !p64_takes(mode, c.one)))
+    L = ws_layout(plan, mode, prec, g, c.nset, c.total_src, *v, true, c.terms(), true);
   if (L.total > 0 && (!ws || ws_bytes < L.total)) return RIME_ERR_WORKSPACE;
   const int64_t nitems = static_cast<int64_t>(c.nset) * g.items_per_set;
   if (nitems <= 0 || nitems > 0x7fffffff) return RIME_ERR_UNSUPPORTED;
@@ -854,7 +1041,12 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
   }
   if (p.pl_a) RIME_HIP(launch_planes(p, stream));
   if (events && plan->ev_main0) RIME_HIP(hipEventRecord(plan->ev_main0, stream));
-  RIME_HIP(launch_variant(mode, prec, vidx, p, static_cast<int>(nitems), stream));
+  if (L.p64) {
+    const rime_status st = enqueue_p64(plan, p, mode, mode, c.total_src, stream);
+    if (st != RIME_OK) return st;
+  } else {
+    RIME_HIP(launch_variant(mode, prec, vidx, p, static_cast<int>(nitems), stream));
+  }
   if (events && plan->ev_main1) RIME_HIP(hipEventRecord(plan->ev_main1, stream));
   if (p.pme_adj) {
     const rime_status st =
@@ -862,7 +1054,12 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
     if (st != RIME_OK) return st;
   }
   if (events && plan->ev_stop) RIME_HIP(hipEventRecord(plan->ev_stop, stream));
-  RIME_HIP(launch_finalize(p, mode, c.max_nsrc, stream, true));
+  if (L.p64 && mode == RIME_MODE_CHI2_GRAD) {
+    RIME_HIP(launch_finalize(p, RIME_MODE_CHI2, c.max_nsrc, stream, true));
+    RIME_HIP(launch_p64_finalize(p, stream));
+  } else {
+    RIME_HIP(launch_finalize(p, mode, c.max_nsrc, stream, true));
+  }
   if (p.pme_adj) RIME_HIP(launch_pme_finalize(p, stream));
   if (p.die_part) RIME_HIP(launch_die_grad(p, stream));
   if (p.gst_part) RIME_HIP(launch_stokes_t_grad(p, stream));
@@ -941,7 +1138,8 @@ struct StreamLayout {
 // Workspace of a streamed call: the domain header, two staging buffers of
 // chunk_t timesteps of data and weights, the per-chunk results, and one
 // chunk-sized call workspace reused by every chunk in stream order.
-StreamLayout stream_layout(const rime_plan *plan, int mode, int prec, int64_t nsrc, int chunk_t) {
+StreamLayout stream_layout(const rime_plan *plan, int mode, int prec, int64_t nsrc, int chunk_t,
+                           bool lean = false) {
   StreamLayout S;
   S.chunk_t = std::max(1, std::min(chunk_t, plan->ntime));
   S.nchunk = (plan->ntime + S.chunk_t - 1) / S.chunk_t;
@@ -961,7 +1159,7 @@ StreamLayout stream_layout(const rime_plan *plan, int mode, int prec, int64_t ns
   off += align_up(static_cast<size_t>(S.nchunk) * S.stride * sizeof(double));
   S.chunk_off = off;
   const rime_plan sp = sub_plan(plan, 0, S.chunk_t);
-  S.chunk_ws = align_up(ws_max(&sp, mode, prec, 1, nsrc));
+  S.chunk_ws = align_up(ws_max(&sp, mode, prec, 1, nsrc, lean));
   off += S.chunk_ws;
   S.total = off;
   return S;
@@ -1102,8 +1300,39 @@ rime_status build_pairs(int na, int nbl, const std::vector<int32_t> &a1,
     }
   }
   pl->ngroup = static_cast<int32_t>(groups.size() / 5);
+  // float64 engine: the baseline of every slot, the 16 x 16 sub-blocks that
+  // hold baselines, and the forward's tasks (pair << 6 | si << 5 | sj << 4 |
+  // fold << 3 | part).  A sub-block on the diagonal without baselines on or
+  // below its own diagonal is folded.
+  std::vector<int32_t> slot_bl(static_cast<size_t>(pl->npair) * kPmeBlk * kPmeBlk, -1);
+  for (int b = 0; b < nbl; ++b) slot_bl[slot[b] >> 1] = b << 1 | (slot[b] & 1);
+  std::vector<int32_t> sub, task4, task1;
+  for (int id = 0; id < pl->npair; ++id)
+    for (int h = 0; h < 4; ++h) {
+      const int si = h >> 1, sj = h & 1;
+      bool any = false, upper = true;
+      for (int i = 0; i < 16; ++i) {
+        const uint32_t m =
+            (mask[static_cast<size_t>(id) * kPmeBlk + 16 * si + i] >> (16 * sj)) & 0xffffu;
+        any = any || m;
+        upper = upper && !(m & ((2u << i) - 1u));
+      }
+      if (!any) continue;
+      sub.push_back(id << 2 | h);
+      const bool fold = pairs[id].x == pairs[id].y && si == sj && upper;
+      const int32_t w = id << 6 | si << 5 | sj << 4 | (fold ? 1 : 0) << 3;
+      task4.push_back(w);
+      for (int part = 0; part < (fold ? 2 : 4); ++part) task1.push_back(w | part);
+    }
+  pl->nsub = static_cast<int32_t>(sub.size());
+  pl->ntask4 = static_cast<int32_t>(task4.size());
+  pl->ntask1 = static_cast<int32_t>(task1.size());
   hipError_t e;
-  if ((e = upload(&pl->d_groups, groups)) != hipSuccess ||
+  if ((e = upload(&pl->d_sub, sub)) != hipSuccess ||
+      (e = upload(&pl->d_slot_bl, slot_bl)) != hipSuccess ||
+      (e = upload(&pl->d_task4, task4)) != hipSuccess ||
+      (e = upload(&pl->d_task1, task1)) != hipSuccess ||
+      (e = upload(&pl->d_groups, groups)) != hipSuccess ||
       (e = upload(&pl->d_pair_blk, pairs)) != hipSuccess ||
       (e = upload(&pl->d_bl_slot, slot)) != hipSuccess ||
       (e = upload(&pl->d_pair_of, pair_id)) != hipSuccess ||
@@ -1186,6 +1415,10 @@ void rime_plan_destroy(rime_plan *plan) {
   (void)hipFree(plan->d_pair_of);
   (void)hipFree(plan->d_pair_mask);
   (void)hipFree(plan->d_groups);
+  (void)hipFree(plan->d_sub);
+  (void)hipFree(plan->d_slot_bl);
+  (void)hipFree(plan->d_task4);
+  (void)hipFree(plan->d_task1);
   (void)hipFree(plan->d_ant_off);
   (void)hipFree(plan->d_ant_bl);
   for (auto &t : plan->tiles) {
@@ -1427,7 +1660,8 @@ rime_status rime_chi2_streamed(const rime_plan *plan, const rime_sky *sky, rime_
   if (st != RIME_OK) return st;
   const int mode = grad ? RIME_MODE_CHI2_GRAD : RIME_MODE_CHI2;
   const int64_t nsrc = sky_nsrc(sky);
-  const StreamLayout S = stream_layout(plan, mode, prec, nsrc, chunk_t);
+  StreamLayout S = stream_layout(plan, mode, prec, nsrc, chunk_t);
+  if (ws_bytes < S.total) S = stream_layout(plan, mode, prec, nsrc, chunk_t, true);
   if (!ws || ws_bytes < S.total) return RIME_ERR_WORKSPACE;
   int dev = 0;
   RIME_HIP(hipGetDevice(&dev));
@@ -1574,13 +1808,15 @@ static int64_t batch_dom_words(const rime_batch *b) {
 // the single-sky pipeline once per set, after a header of domain flags, with
 // one set's layout per lane (each reused in stream order); the others run
 // all sets in one launch sequence.
-static size_t batch_ws(const rime_batch *b, int mode, int prec, int vidx, int fidx) {
+static size_t batch_ws(const rime_batch *b, int mode, int prec, int vidx, int fidx,
+                       bool lean = false) {
   const Variant *v = variant_info(mode, prec, vidx);
   if (!v) return 0;
   if (per_set_variant(b->plan, mode, prec, *v))
     return align_up(static_cast<size_t>(batch_dom_words(b)) * sizeof(int32_t)) +
-           batch_lanes(b) * align_up(call_ws(b->plan, mode, prec, vidx, fidx, 1, b->max_nsrc));
-  return call_ws(b->plan, mode, prec, vidx, fidx, b->nset, b->total_src);
+           batch_lanes(b) *
+               align_up(call_ws(b->plan, mode, prec, vidx, fidx, 1, b->max_nsrc, 0, lean));
+  return call_ws(b->plan, mode, prec, vidx, fidx, b->nset, b->total_src, 0, lean);
 }
 
 static int batch_variant(const rime_batch *b, int mode, int prec) {
@@ -1609,7 +1845,8 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
   const int fidx = plan->variant[RIME_MODE_CHI2][prec];
   const Variant *v = variant_info(mode, prec, vidx);
   if (!v) return RIME_ERR_UNSUPPORTED;
-  if (!ws || ws_bytes < batch_ws(b, mode, prec, vidx, fidx)) return RIME_ERR_WORKSPACE;
+  const bool lean = ws_bytes < batch_ws(b, mode, prec, vidx, fidx);
+  if (!ws || ws_bytes < batch_ws(b, mode, prec, vidx, fidx, lean)) return RIME_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const bool per_set = per_set_variant(plan, mode, prec, *v);
   const int lanes = per_set ? batch_lanes(b) : 1;
@@ -1635,7 +1872,8 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
     // domain header); the timing events (if any) bracket the whole sequence
     // on the caller's stream
     const size_t hdr = align_up(static_cast<size_t>(batch_dom_words(b)) * sizeof(int32_t));
-    const size_t lane_bytes = align_up(call_ws(plan, mode, prec, vidx, fidx, 1, b->max_nsrc));
+    const size_t lane_bytes =
+        align_up(call_ws(plan, mode, prec, vidx, fidx, 1, b->max_nsrc, 0, lean));
     const int32_t nwords = static_cast<int32_t>(batch_dom_words(b) - 1);
     if (plan->ev_start) RIME_HIP(hipEventRecord(plan->ev_start, s));
     if (lanes > 1) {

@@ -153,6 +153,24 @@ struct KParams {
   // [pme_nt][nchan][pl_ns][nap], or nullptr: rime_main stages from them
   float2 *pl_a;
   int32_t pl_s0, pl_ns;
+  // float64 engine (rime_p64.hip): planes of every source [pme_nt][nchan]
+  // [nap][p64_ns] (k3 in gradient calls with a beam), the baselines' vectors
+  // and the weighted residual in Stokes form by antenna-pair slot
+  int32_t p64_ns;          // sources, padded to whole 128-byte lines
+  double2 *p64_a;
+  double *p64_k3;
+  double2 *p64_geo;        // [ntime][npair][kPmeBlk][kPmeBlk] (u_p - u_q, v_p - v_q)
+  double2 *p64_rho;        // [pme_nt][nchan][npair][kPmeBlk][kPmeBlk][4], conjugated for
+                           //   baselines stored as (q, p)
+  const int32_t *slot_bl;  // [npair][kPmeBlk][kPmeBlk] baseline << 1 | stored as (q, p), or -1
+  int32_t nsub;            // 16 x 16 antenna sub-blocks that hold baselines
+  const int32_t *sub;      // [nsub] pair << 2 | row half << 1 | column half
+  int32_t p64_nr, p64_ntask, p64_tch;  // forward: baselines per lane, tasks, timesteps per item
+  const int32_t *p64_task;             // [ntask], see task_of
+  int64_t p64_item0;                   // first chi^2 partial of this pass
+  int32_t p64_ncw, p64_ncg, p64_nsg;   // adjoint: channels per item, groups, source groups
+  int32_t p64_split;                   // parts of a sub-block (1, or 8 in small calls)
+  double *p64_part;        // [nsg][ntime][ncg][nsub][split][10][64] gradient partials
 };
 
 // Antenna block of the matrix-core engine (rows and columns of one MFMA tile),

@@ -32,6 +32,7 @@ namespace rime {
 
 template <class R>
 __device__ void prep_baselines(const KParams &p, int nc, int t);
+__device__ void prep_slots(const KParams &p, int t);
 
 // ---------------------------------------------------------------------------
 // Per-call preparation, one launch.  Rows blockIdx.y < nset: per-source data,
@@ -47,7 +48,10 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
   using R4 = typename Num<R>::R4;
   const int set = blockIdx.y;
   if (set >= p.nset) {
-    prep_baselines<R>(p, nc, set - p.nset);
+    if (sizeof(R) == 8 && p.p64_geo)
+      prep_slots(p, set - p.nset);
+    else
+      prep_baselines<R>(p, nc, set - p.nset);
     return;
   }
   const SetDesc sd = p.sets ? p.sets[set] : p.one;
@@ -67,7 +71,11 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
     const double I = sd.stokes[4 * s], Q = sd.stokes[4 * s + 1];
     const double U = sd.stokes[4 * s + 2], V = sd.stokes[4 * s + 3];
     const double a = sd.alpha[s];
-    R4 *st = static_cast<R4 *>(p.src_st) + g * p.nchan;
+    // [source][channel]; [channel][source] for the float64 engine, whose loops
+    // run over the sources of a channel
+    const int64_t row = p.p64_ns ? 0 : g * p.nchan, step = p.p64_ns ? p.p64_ns : 1;
+    R4 *st = static_cast<R4 *>(p.src_st) + row + (p.p64_ns ? s : 0);
+    R *sf = static_cast<R *>(p.src_sf) + row + (p.p64_ns ? s : 0);
     for (int c = 0; c < p.nchan; ++c) {
       const double f = exp(a * p.lnfr[c]);
       R4 v;
@@ -75,9 +83,9 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
       v.y = static_cast<R>(f * Q);
       v.z = static_cast<R>(f * U);
       v.w = static_cast<R>(f * V);
-      st[c] = v;
+      st[c * step] = v;
       if (p.src_f) p.src_f[g * p.nchan + c] = static_cast<float>(f);
-      if (p.src_sf) static_cast<R *>(p.src_sf)[g * p.nchan + c] = static_cast<R>(f);
+      if (p.src_sf) sf[c * step] = static_cast<R>(f);
     }
     if (s >= sd.npsrc) {
       // Gaussian or disk shape with the axis ratio folded into the minor-axis
@@ -141,19 +149,26 @@ __device__ void prep_baselines(const KParams &p, int nc, int t) {
   }
 }
 
+// The float64 engine's records of timestep t: the baseline vector
+// (u_p - u_q, v_p - v_q) of every antenna-pair slot.
+__device__ void prep_slots(const KParams &p, int t) {
+  const int n = p.npair * kPmeBlk * kPmeBlk;
+  const double *uvw = p.uvw + static_cast<int64_t>(t) * p.na * 3;
+  for (int i = static_cast<int>(blockIdx.x * 256 + threadIdx.x); i < n;
+       i += static_cast<int>(gridDim.x) * 256) {
+    const int pair = i / (kPmeBlk * kPmeBlk);
+    const int2 blk = p.pair_blk[pair];
+    const int a = blk.x * kPmeBlk + i / kPmeBlk % kPmeBlk, b = blk.y * kPmeBlk + i % kPmeBlk;
+    double2 d = make_double2(0.0, 0.0);
+    if (a < p.na && b < p.na)
+      d = make_double2(uvw[3 * a] - uvw[3 * b], uvw[3 * a + 1] - uvw[3 * b + 1]);
+    p.p64_geo[static_cast<int64_t>(t) * n + i] = d;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Main kernel
 // ---------------------------------------------------------------------------
-
-// Kernel modes.  MODE_RESID is the forward of the float64-residual mixed
-// mode: float64 arithmetic over float32 data and weights, chi^2 partials and,
-// when p.rho_b is set, the weighted residual in Stokes form (float32) per
-// visibility and, with p.pme_adj, in the antenna-pair slots.  MODE_ADJ is its
-// float32 adjoint: pass 2 alone, over the residual read from p.rho_b.
-enum { MODE_PREDICT = 0, MODE_CHI2 = 1, MODE_GRAD = 2, MODE_RESID = 3, MODE_ADJ = 4 };
-
-template <bool B, class X, class Y> struct Pick { using T = X; };
-template <class X, class Y> struct Pick<false, X, Y> { using T = Y; };
 
 template <class R, int NBT, int NC, int NS, int MODE>
 struct Layout {
@@ -593,22 +608,6 @@ __device__ inline void adjoint_pair(int wave, int nw, int nact, int hb, const fl
   if ((nact & 1) && hb == 0 && wave == npair % nw) body(rec[nact - 1], nact - 1);
 }
 
-// Source tiles of a set: points first, then Gaussians, then disks; tile k
-// covers sources [s0, s0 + cnt) of one morphology.
-struct SrcTile {
-  int shape, s0, cnt;
-};
-
-__device__ inline SrcTile src_tile(const SetDesc &sd, int k, int ns, int npt, int ngt) {
-  if (k < npt) return {SHAPE_POINT, k * ns, min(ns, sd.npsrc - k * ns)};
-  if (k < npt + ngt) {
-    const int s0 = sd.npsrc + (k - npt) * ns;
-    return {SHAPE_GAUSS, s0, min(ns, sd.npsrc + sd.ngsrc - s0)};
-  }
-  const int s0 = sd.npsrc + sd.ngsrc + (k - npt - ngt) * ns;
-  return {SHAPE_DISK, s0, min(ns, sd.npsrc + sd.ngsrc + sd.nxsrc - s0)};
-}
-
 // TERMS: the instantiation that also applies per-call terms (a 2x2 G per
 // antenna, brightness per timestep); kept apart so that the plain calls do
 // not carry their registers.
@@ -627,7 +626,6 @@ void rime_main(const KParams p) {
   using R4 = typename N::R4;
   // data and weights: float32 in the float64 forward of the float64-residual mode
   using DT = typename Pick<MODE == MODE_RESID, float, R>::T;
-  using DT2 = typename Num<DT>::R2;
   constexpr int NAT = L::NAT;
   constexpr int NW = L::NW;
 
@@ -717,157 +715,39 @@ void rime_main(const KParams p) {
     // the global antennas of this thread's baseline
     const int gap = active ? p.tile_ant[tile * NAT + lp] : 0;
     const int gaq = active ? p.tile_ant[tile * NAT + lq] : 0;
-    auto gains = [&](double2 (&gg)[4]) {
-      // V_ij *= g_pi conj(g_qj)
-      const double2 gpi[2] = {make_double2(p.gains[4 * gap + 0], p.gains[4 * gap + 1]),
-                              make_double2(p.gains[4 * gap + 2], p.gains[4 * gap + 3])};
-      const double2 gqj[2] = {make_double2(p.gains[4 * gaq + 0], p.gains[4 * gaq + 1]),
-                              make_double2(p.gains[4 * gaq + 2], p.gains[4 * gaq + 3])};
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const double2 a = gpi[i], b = gqj[j];
-          gg[2 * i + j] = make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
-        }
-    };
     auto epilogue = [&](int c, const double (&S)[8], const double2 (&gg)[4]) {
       const bool ok = c < ncv;
-      // Stokes sums -> 2x2 coherency X (eq. brightness_term)
-      const double SIr = S[0], SIi = S[1], SQr = S[2], SQi = S[3];
-      const double SUr = S[4], SUi = S[5], SVr = S[6], SVi = S[7];
-      M22 X;
-      X.re[0] = SIr + SQr;  // xx
-      X.im[0] = SIi + SQi;
-      X.re[1] = SUr - SVi;  // xy = S_U + i S_V
-      X.im[1] = SUi + SVr;
-      X.re[2] = SUr + SVi;  // yx = S_U - i S_V
-      X.im[2] = SUi - SVr;
-      X.re[3] = SIr - SQr;  // yy
-      X.im[3] = SIi - SQi;
-      double Vr[4], Vi[4];
-      // V = G_p X G_q^H (eq. 1's direction-independent term, outside the
-      // source sum), or the plan's diagonal gains
-      M22 Gp, Gq;
-      if (TERMS && p.die) {
-        const int64_t gi = (static_cast<int64_t>(t) * p.na) * p.nchan + c0 + min(c, ncv - 1);
-        Gp = m22_load(p.die + (gi + static_cast<int64_t>(gap) * p.nchan) * 4);
-        Gq = m22_load(p.die + (gi + static_cast<int64_t>(gaq) * p.nchan) * 4);
-        const M22 V = m22_mul(m22_mul(Gp, X), m22_herm(Gq));
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          Vr[k] = V.re[k];
-          Vi[k] = V.im[k];
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          Vr[k] = X.re[k] * gg[k].x - X.im[k] * gg[k].y;
-          Vi[k] = X.re[k] * gg[k].y + X.im[k] * gg[k].x;
-        }
-      }
       const int64_t vidx = ((static_cast<int64_t>(t) * p.nbl + bl) * p.nchan + c0 + c) * 4;
-      if (MODE == MODE_PREDICT) {
-        if (ok) {
-          R2 *out = static_cast<R2 *>(p.vis) + vidx;
+      // rho_k in the adjoint's precision (float32 in both mixed modes)
+      using A = typename Pick<MODE == MODE_RESID, float, R>::T;
+      using A2 = typename Num<A>::R2;
+      A2 v[4];
+      visibility<R, DT, A, MODE == MODE_PREDICT, MODE == MODE_GRAD || MODE == MODE_RESID, TERMS>(
+          p, ok, t, gap, gaq, c0 + min(c, ncv - 1), vidx, S, gg, chi, v);
+      if (MODE == MODE_GRAD || MODE == MODE_RESID) {
+        if (MODE == MODE_GRAD) {
+          A2 *rho = reinterpret_cast<A2 *>(s_rho) + (tid * NC + c) * 4;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            R2 v;
-            v.x = static_cast<R>(Vr[k]);
-            v.y = static_cast<R>(Vi[k]);
-            out[k] = v;
-          }
+          for (int kk = 0; kk < 4; ++kk) rho[kk] = v[kk];
+        } else if (ok && p.rho_b) {
+          float2 *rb = p.rho_b + rho_set + vidx;
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) rb[kk] = make_float2(v[kk].x, v[kk].y);
         }
-      } else {
-        double Yr[4] = {0, 0, 0, 0}, Yi[4] = {0, 0, 0, 0};
-        if (ok) {
-          const DT2 *D = static_cast<const DT2 *>(p.data) + vidx;
-          const DT *W = static_cast<const DT *>(p.weight) + vidx;
+        if (sizeof(A) == 4 && p.pme_adj && ok) {
+          // the point-source adjoint on the matrix cores reads rho from its
+          // antenna-pair slot (conjugated when the slot holds (q, p))
+          const int slot = p.bl_slot[bl];
+          const int pair = slot >> 11, si = (slot >> 6) & 31, sj = (slot >> 1) & 31;
+          const float cj = (slot & 1) ? -1.0f : 1.0f;
+          float2 *rt = p.rho_t +
+                       (((static_cast<int64_t>(t) * p.nchan + c0 + c) * p.npair + pair) * 4) *
+                           (kPmeBlk * kPmeBlk) +
+                       si * kPmeBlk + sj;
 #pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const DT2 d = D[k];
-            const double w = static_cast<double>(W[k]);
-            const double rr = Vr[k] - static_cast<double>(d.x);
-            const double ri = Vi[k] - static_cast<double>(d.y);
-            chi.add(w * (rr * rr + ri * ri));
-            Yr[k] = w * rr;
-            Yi[k] = w * ri;
-          }
-        }
-        if (MODE == MODE_GRAD || MODE == MODE_RESID) {
-          // the residual carried to the coherency X: Z = G_p^H Y G_q (with
-          // diagonal gains Z_ij = Y_ij conj(g_pi) g_qj = Y_ij conj(gg_ij)); then
-          // rho_I = conj(Zxx) + conj(Zyy), rho_Q = conj(Zxx) - conj(Zyy),
-          // rho_U = conj(Zxy) + conj(Zyx), rho_V = i (conj(Zxy) - conj(Zyx))
-          double Zr[4], Zi[4];
-          if (TERMS && p.die) {
-            M22 Y;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              Y.re[k] = Yr[k];
-              Y.im[k] = Yi[k];
-            }
-            const M22 Z = m22_mul(m22_mul(m22_herm(Gp), Y), Gq);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              Zr[k] = Z.re[k];
-              Zi[k] = Z.im[k];
-            }
-            if (ok && p.die_part) {
-              // d chi^2 / d conj(G) of this visibility: Y G_q X^H for antenna
-              // p and Y^H G_p X for antenna q
-              const M22 Ap = m22_mul(m22_mul(Y, Gq), m22_herm(X));
-              const M22 Aq = m22_mul(m22_mul(m22_herm(Y), Gp), X);
-              double2 *dp = p.die_part + vidx * 2;
-#pragma unroll
-              for (int k = 0; k < 4; ++k) {
-                dp[k] = make_double2(Ap.re[k], Ap.im[k]);
-                dp[4 + k] = make_double2(Aq.re[k], Aq.im[k]);
-              }
-            }
-          } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-              Zr[k] = Yr[k] * gg[k].x + Yi[k] * gg[k].y;
-              Zi[k] = Yi[k] * gg[k].x - Yr[k] * gg[k].y;
-            }
-          }
-          // rho_k in the adjoint's precision (float32 in both mixed modes)
-          using A = typename Pick<MODE == MODE_RESID, float, R>::T;
-          using A2 = typename Num<A>::R2;
-          A2 v[4];
-          v[0].x = static_cast<A>(Zr[0] + Zr[3]);
-          v[0].y = static_cast<A>(-(Zi[0] + Zi[3]));
-          v[1].x = static_cast<A>(Zr[0] - Zr[3]);
-          v[1].y = static_cast<A>(-(Zi[0] - Zi[3]));
-          v[2].x = static_cast<A>(Zr[1] + Zr[2]);
-          v[2].y = static_cast<A>(-(Zi[1] + Zi[2]));
-          v[3].x = static_cast<A>(Zi[1] - Zi[2]);
-          v[3].y = static_cast<A>(Zr[1] - Zr[2]);
-          if (MODE == MODE_GRAD) {
-            A2 *rho = reinterpret_cast<A2 *>(s_rho) + (tid * NC + c) * 4;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) rho[kk] = v[kk];
-          } else if (ok && p.rho_b) {
-            float2 *rb = p.rho_b + rho_set + vidx;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) rb[kk] = make_float2(v[kk].x, v[kk].y);
-          }
-          if (sizeof(A) == 4 && p.pme_adj && ok) {
-            // the point-source adjoint on the matrix cores reads rho from its
-            // antenna-pair slot (conjugated when the slot holds (q, p))
-            const int slot = p.bl_slot[bl];
-            const int pair = slot >> 11, si = (slot >> 6) & 31, sj = (slot >> 1) & 31;
-            const float cj = (slot & 1) ? -1.0f : 1.0f;
-            float2 *rt = p.rho_t +
-                         (((static_cast<int64_t>(t) * p.nchan + c0 + c) * p.npair + pair) * 4) *
-                             (kPmeBlk * kPmeBlk) +
-                         si * kPmeBlk + sj;
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk)
-              rt[kk * kPmeBlk * kPmeBlk] =
-                  make_float2(static_cast<float>(v[kk].x), cj * static_cast<float>(v[kk].y));
-          }
+          for (int kk = 0; kk < 4; ++kk)
+            rt[kk * kPmeBlk * kPmeBlk] =
+                make_float2(static_cast<float>(v[kk].x), cj * static_cast<float>(v[kk].y));
         }
       }
     };
@@ -960,7 +840,7 @@ void rime_main(const KParams p) {
           }
         }
         double2 gg[4];
-        gains(gg);
+        gain_products(p, gap, gaq, gg);
 #pragma unroll
         for (int c = 0; c < NC; ++c) epilogue(c, acc[c], gg);
       }

@@ -160,6 +160,24 @@ __global__ __launch_bounds__(256) void pme_phase(const KParams p) {
   }
 }
 
+// St'_k (k = I, Q, U, V) of source s of the set at channel c and timestep t:
+// the spectrally scaled Stokes vector, or, with brightness per timestep (ST),
+// the spectral factor times that timestep's Stokes vector (rounded as in the
+// per-baseline kernels).  The kernels that call it per chunk take ST as a
+// template parameter, so that the plain calls do not carry its registers.
+template <bool ST>
+__device__ inline float4 pme_stokes(const KParams &p, int s, int c, int t) {
+  const int64_t gs = p.one.src_off + s;
+  if (ST) {
+    const int nsrc = p.one.npsrc + p.one.ngsrc + p.one.nxsrc;
+    const double *q = p.stokes_t + (static_cast<int64_t>(t) * nsrc + s) * 4;
+    const double f = static_cast<double>(static_cast<const float *>(p.src_sf)[gs * p.nchan + c]);
+    return make_float4(static_cast<float>(f * q[0]), static_cast<float>(f * q[1]),
+                       static_cast<float>(f * q[2]), static_cast<float>(f * q[3]));
+  }
+  return static_cast<const float4 *>(p.src_st)[gs * p.nchan + c];
+}
+
 // ---------------------------------------------------------------------------
 // Forward scale: exponent e of max_s |St'_k,s(nu)| (over the timesteps too with
 // brightness per timestep), one workgroup per channel.
@@ -172,8 +190,7 @@ __global__ __launch_bounds__(256) void pme_scale(const KParams p) {
   float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
   for (int t = 0; t < nt; ++t)
     for (int s = threadIdx.x; s < sd.npsrc; s += 256) {
-      const float4 v = p.stokes_t ? pme_stokes<true, float>(p, s, c, t)
-                                  : pme_stokes<false, float>(p, s, c, t);
+      const float4 v = p.stokes_t ? pme_stokes<true>(p, s, c, t) : pme_stokes<false>(p, s, c, t);
       m[0] = fmaxf(m[0], fabsf(v.x));
       m[1] = fmaxf(m[1], fabsf(v.y));
       m[2] = fmaxf(m[2], fabsf(v.z));
@@ -249,7 +266,7 @@ __device__ inline FwdRegs fwd_load(const KParams &p, const uint32_t *hi0, const 
         r.pbl = *reinterpret_cast<const uint4 *>(lo0 + row + Pb * kPmeBlk + ag);
       }
     }
-    r.st = pme_stokes<ST, float>(p, s0 + s, c, t);
+    r.st = pme_stokes<ST>(p, s0 + s, c, t);
   }
   return r;
 }
@@ -645,7 +662,7 @@ __global__ __launch_bounds__(256, 2) void pme_adjoint(const KParams p) {
           float f = 0.0f;
           if (s < cnt) {
             const int64_t gs = sd.src_off + s0 + s;
-            sv = pme_stokes<ST, float>(p, s0 + s, c, t);
+            sv = pme_stokes<ST>(p, s0 + s, c, t);
             lo = p.src_lon[gs];
             f = p.src_f[gs * p.nchan + c];
           }

@@ -1,0 +1,126 @@
+"""The float64 engine of large arrays (16 x 16 antenna sub-blocks, planes of
+per-antenna terms) against the per-baseline kernel (variant 0, which never
+takes it) and, on one case per kind, the oracle: visibilities, chi^2 and
+gradient to the float64 bar of 1e-12 (float64 sums of at most 200 terms carry
+200 x 2^-53 = 2e-14)."""
+import numpy as np
+import pytest
+
+import oracle.rime_oracle as O
+from rime_synth import Observation, add_disks, make_problem, random_die, rngs, stokes_per_time
+from tests._helpers import TOL, grad_errors, rel, vis_error
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+R = pytest.importorskip("paper_1501_07719_amd")
+
+
+def shuffled(obs):
+    """300 baselines in random order, half of them swapped, one autocorrelation:
+    sub-blocks with baselines on and below their diagonal."""
+    rng = np.random.default_rng(3)
+    pick = rng.permutation(obs.nbl)[:300]
+    a1, a2 = obs.ant1[pick].copy(), obs.ant2[pick].copy()
+    sw = rng.random(300) < 0.5
+    a1[sw], a2[sw] = a2[sw], a1[sw].copy()
+    return Observation(**{**obs.__dict__, "ant1": np.append(a1, 5).astype(np.int32),
+                          "ant2": np.append(a2, 5).astype(np.int32)})
+
+
+def run(obs, sky, D, W, variant, terms=None, ws_bytes=None):
+    plan = R.Plan(obs)
+    for mode in (R.MODE_PREDICT, R.MODE_CHI2, R.MODE_CHI2_GRAD):
+        plan.set_variant(mode, R.FP64, variant)
+    s = R.DeviceSky.from_host(sky)
+    f64 = dict(dtype=torch.float64, device="cuda")
+    shape = (obs.ntime, obs.nbl, obs.nchan, 4)
+    vis = torch.full(shape, float("nan"), dtype=torch.complex128, device="cuda")
+    Dd, Wd = torch.as_tensor(D, device="cuda"), torch.as_tensor(W, device="cuda")
+    c1, c2 = torch.empty(1, **f64), torch.empty(1, **f64)
+    grad = torch.full((sky.nsrc, 10), float("nan"), **f64)
+    out = {}
+    if terms is None:
+        n = ws_bytes or plan.workspace_size(R.MODE_CHI2_GRAD, R.FP64, 1, sky.nsrc)
+        ws = torch.empty(max(n, plan.workspace_size(R.MODE_PREDICT, R.FP64, 1, sky.nsrc)
+                             if ws_bytes is None else n), dtype=torch.uint8, device="cuda")
+        R.rime_predict(plan, s, R.FP64, vis, ws)
+        R.rime_chi2(plan, s, R.FP64, Dd, Wd, c1, ws)
+        R.rime_chi2_grad(plan, s, R.FP64, Dd, Wd, c2, grad, ws)
+    else:
+        t = {k: torch.as_tensor(v, device="cuda") for k, v in terms.items()}
+        g = {f"grad_{k}": torch.full_like(v, float("nan")) for k, v in t.items()}
+        kw = {k: True for k in (*t, *g)}
+        ws = torch.empty(R.rime_workspace_size_ex(plan, R.MODE_CHI2_GRAD, R.FP64, sky.nsrc, **kw),
+                         dtype=torch.uint8, device="cuda")
+        R.rime_predict_ex(plan, s, R.FP64, vis, ws, **t)
+        R.rime_chi2_ex(plan, s, R.FP64, Dd, Wd, c1, None, ws, **t)
+        R.rime_chi2_ex(plan, s, R.FP64, Dd, Wd, c2, grad, ws, **t, **g)
+        out = {k: v.cpu().numpy() for k, v in g.items()}
+    torch.cuda.synchronize()
+    out.update(vis=vis.cpu().numpy(), chi2=c1.item(), chi2_g=c2.item(), grad=grad.cpu().numpy())
+    plan.close()
+    return out
+
+
+def problem(na, ntime, nchan, npsrc, ng, nx, kind, beam=True):
+    pr = make_problem("c1", ntime=ntime, nchan=nchan, npsrc=npsrc, ngsrc=ng, na=na, key=95)
+    obs = shuffled(pr.obs) if kind == "shuffled" else pr.obs
+    if not beam:
+        obs = Observation(**{**obs.__dict__, "beam": False, "pointing": None})
+    sky = add_disks(pr.sky, nx, rngs(95)[5])
+    rng = np.random.default_rng(4)
+    shape = (ntime, obs.nbl, nchan, 4)
+    D = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+    W = rng.uniform(0.0, 2.0, shape)
+    return obs, sky, D, W
+
+
+def check(a, b, obs, sky):
+    assert vis_error(a["vis"], b["vis"], sky, obs) <= TOL[0]
+    assert rel(a["chi2"], b["chi2"]) <= TOL[0] and rel(a["chi2_g"], b["chi2"]) <= TOL[0]
+    errs = grad_errors(a["grad"], b["grad"], sky.npsrc)
+    assert max(errs.values()) <= TOL[0], errs
+    for k in a:
+        if k.startswith("grad_"):
+            assert np.linalg.norm(a[k] - b[k]) <= TOL[0] * np.linalg.norm(b[k]), k
+
+
+# ragged sub-blocks (15 and 17 antennas), source groups (63, 64, 65 of 64),
+# channel quads, one baseline per lane (few wavefronts) and four, split
+# sub-blocks of the adjoint and whole ones, folded diagonal sub-blocks and not
+@pytest.mark.parametrize("na,ntime,nchan,npsrc,ng,nx,kind", [
+    (15, 1, 1, 40, 0, 0, ""), (16, 2, 3, 32, 31, 33, ""), (17, 1, 5, 65, 63, 0, ""),
+    (33, 3, 4, 64, 0, 64, ""), (50, 2, 7, 100, 40, 60, "shuffled"),
+    (40, 40, 33, 35, 34, 0, ""), (64, 9, 90, 33, 40, 1, "")])
+def test_engine_equals_per_baseline_kernel(na, ntime, nchan, npsrc, ng, nx, kind):
+    obs, sky, D, W = problem(na, ntime, nchan, npsrc, ng, nx, kind, beam=nchan != 3)
+    check(run(obs, sky, D, W, 1), run(obs, sky, D, W, 0), obs, sky)
+
+
+def test_engine_terms():
+    obs, sky, D, W = problem(18, 3, 5, 70, 50, 40, "")
+    rng = np.random.default_rng(5)
+    terms = dict(die=random_die(3, 18, 5, rng), stokes_t=stokes_per_time(sky, 3, rng))
+    check(run(obs, sky, D, W, 1, terms), run(obs, sky, D, W, 0, terms), obs, sky)
+
+
+@pytest.mark.parametrize("kind", ["", "shuffled"])
+def test_engine_oracle(kind):
+    obs, sky, D, W = problem(26, 1, 2, 50, 40, 38, kind)
+    got = run(obs, sky, D, W, 1)
+    c, g = O.chi2_and_grad(obs, sky, D, W)
+    check(got, dict(vis=O.model_vis(obs, sky), chi2=c, grad=g), obs, sky)
+
+
+def test_small_workspace_runs_without_the_planes():
+    """A workspace that holds the per-baseline kernel's regions but not the
+    planes still serves the call."""
+    obs, sky, D, W = problem(30, 2, 6, 64, 0, 0, "")
+    plan = R.Plan(obs)
+    full = plan.workspace_size(R.MODE_CHI2_GRAD, R.FP64, 1, sky.nsrc)
+    plan.close()
+    a, b = run(obs, sky, D, W, 1), run(obs, sky, D, W, 1, ws_bytes=full // 2)
+    check(a, b, obs, sky)
+    with pytest.raises(R.RimeError):
+        run(obs, sky, D, W, 1, ws_bytes=4096)
