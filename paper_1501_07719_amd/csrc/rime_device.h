@@ -571,6 +571,29 @@ __device__ inline int xcd_item(int nitems) {
   return static_cast<int>(blockIdx.x % 8) * per_xcd + static_cast<int>(blockIdx.x / 8);
 }
 
+// chi^2 of one set from its per-item (sum, compensation) partials, in a fixed
+// order; all 256 threads of the workgroup take part.
+__device__ inline void chi2_reduce(const KParams &p, int set, double2 *scr) {
+  Comp acc;
+  const double2 *part = p.chi2_part + static_cast<int64_t>(set) * p.chi2_items;
+  // each thread merges items tid, tid + 256, ... in that order; four loads are
+  // issued before they are merged
+  int i = threadIdx.x;
+  for (; i + 3 * 256 < p.chi2_items; i += 4 * 256) {
+    double2 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = part[i + k * 256];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.merge(v[k].x, v[k].y);
+  }
+  for (; i < p.chi2_items; i += 256) {
+    const double2 v = part[i];
+    acc.merge(v.x, v.y);
+  }
+  const Comp r = block_reduce<256>(acc, scr);
+  if (threadIdx.x == 0) p.chi2_out[set] = r.s + r.c;
+}
+
 constexpr int nat_for(int nbt) { return nbt >= 1024 ? 64 : nbt >= 256 ? 32 : 16; }
 
 }  // namespace rime

@@ -22,8 +22,6 @@ hipError_t launch_finalize(const KParams &p, int mode, int max_nsrc, hipStream_t
                            bool with_chi2);
 hipError_t launch_pme(const KParams &p, hipStream_t stream);
 hipError_t launch_pme_adjoint(const KParams &p, bool phase, hipStream_t stream);
-hipError_t launch_pme_finalize(const KParams &p, hipStream_t stream);
-hipError_t launch_pme_scale(const KParams &p, hipStream_t stream);
 hipError_t launch_planes(const KParams &p, hipStream_t stream);
 hipError_t launch_p64_planes(const KParams &p, hipStream_t stream);
 hipError_t launch_p64_forward(const KParams &p, int mode, hipStream_t stream);
@@ -796,6 +794,7 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
   p.tchunk = g.tchunk;
   p.ntc = g.ntc;
   p.items_per_set = g.items_per_set;
+  p.chi2_items = g.items_per_set;
   p.nset = c.nset;
   p.sets = c.d_sets;
   p.one = c.one;
@@ -848,7 +847,7 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
     p.p64_ntask = pg.ntask;
     p.p64_task = pg.nr == 4 ? plan->d_task4 : plan->d_task1;
     p.p64_tch = pg.tch;
-    p.items_per_set = static_cast<int32_t>(pg.nitem);
+    p.chi2_items = static_cast<int32_t>(pg.nitem);
     if (c.mode == RIME_MODE_CHI2_GRAD) {
       if (L.has_k3) p.p64_k3 = reinterpret_cast<double *>(w + L.p64_k3);
       p.p64_geo = reinterpret_cast<double2 *>(w + L.p64_geo);
@@ -998,10 +997,12 @@ rime_status enqueue_res64(const rime_plan *plan, const Call &c, int vidx, void *
     RIME_HIP(launch_adj(vidx, pa, static_cast<int>(na), stream));
   }
   if (events && plan->ev_stop) RIME_HIP(hipEventRecord(plan->ev_stop, stream));
-  RIME_HIP(launch_finalize(pf, RIME_MODE_CHI2, c.max_nsrc, stream, true));
+  if (!grad) RIME_HIP(launch_finalize(pf, RIME_MODE_CHI2, c.max_nsrc, stream, true));
   if (grad) {
-    RIME_HIP(launch_finalize(pa, RIME_MODE_CHI2_GRAD, c.max_nsrc, stream, false));
-    if (pa.pme_adj) RIME_HIP(launch_pme_finalize(pa, stream));
+    // the forward's chi^2 partials are summed beside the adjoint's
+    pa.chi2_part = pf.chi2_part;
+    pa.chi2_items = pf.chi2_items;
+    RIME_HIP(launch_finalize(pa, RIME_MODE_CHI2_GRAD, c.max_nsrc, stream, true));
     if (pf.die_part) RIME_HIP(launch_die_grad(pf, stream));
     if (pa.gst_part) RIME_HIP(launch_stokes_t_grad(pa, stream));
   }
@@ -1028,7 +1029,6 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
                        mode == RIME_MODE_CHI2_GRAD ? v->nc : 0, stream));
   if (events && plan->ev_start) RIME_HIP(hipEventRecord(plan->ev_start, stream));
   if (p.pme) {
-    RIME_HIP(launch_pme_scale(p, stream));
     KParams pf = p;
     // with one pass over time the adjoint reuses the forward's phase planes,
     // which then carry the beam-derivative plane too
@@ -1054,13 +1054,10 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
     if (st != RIME_OK) return st;
   }
   if (events && plan->ev_stop) RIME_HIP(hipEventRecord(plan->ev_stop, stream));
-  if (L.p64 && mode == RIME_MODE_CHI2_GRAD) {
-    RIME_HIP(launch_finalize(p, RIME_MODE_CHI2, c.max_nsrc, stream, true));
+  if (L.p64 && mode == RIME_MODE_CHI2_GRAD)
     RIME_HIP(launch_p64_finalize(p, stream));
-  } else {
+  else
     RIME_HIP(launch_finalize(p, mode, c.max_nsrc, stream, true));
-  }
-  if (p.pme_adj) RIME_HIP(launch_pme_finalize(p, stream));
   if (p.die_part) RIME_HIP(launch_die_grad(p, stream));
   if (p.gst_part) RIME_HIP(launch_stokes_t_grad(p, stream));
   return RIME_OK;

@@ -108,7 +108,9 @@ struct KParams {
   const void *data;        // [ntime][nbl][nchan][4] complex
   const void *weight;      // [ntime][nbl][nchan][4] real
   void *vis;               // predict output
-  double2 *chi2_part;      // [total items] (sum, compensation)
+  double2 *chi2_part;      // [nset][chi2_items] (sum, compensation)
+  int32_t chi2_items;      // chi^2 partials per set
+  int32_t fin_chi2;        // finalize_grad1: sets whose chi^2 it forms (set at launch)
   double *grad_part;       // gradient partials [set][item][nsrc][10]
   void *rho_g;             // float64 gradient: residual tile per work item
                            //   [item][nbt][nc][4] double2
@@ -186,11 +188,13 @@ constexpr int kPmeNCW = 4;
 
 // The sums of the adjoint partials over items run as about kPmeFinWG
 // workgroups of 256 columns (kPmeSR * 7 = 14 x 256) before one pass over the
-// chunks: nsr * chunks <= max(kPmeFinWG, nsr) chunk rows of kPmeSR * 7.
+// chunks: nsr * chunks <= max(kPmeFinWG, nsr) chunk rows of kPmeSR * 7.  A
+// chunk holds eight items at least, so that neither pass is a long chain (48
+// items in one chunk each took the second pass 32 us).
 constexpr int kPmeFinWG = 2048 / (kPmeSR * 7 / 256);
 inline int pme_fin_nchunk(int nsr, int64_t nper) {
-  const int64_t n = kPmeFinWG / (nsr > 0 ? nsr : 1);
-  return static_cast<int>(n < 1 ? 1 : n < nper ? n : (nper > 0 ? nper : 1));
+  const int64_t n = kPmeFinWG / (nsr > 0 ? nsr : 1), m = (nper + 7) / 8;
+  return static_cast<int>(n < 1 ? 1 : n < m ? n : (m > 0 ? m : 1));
 }
 
 // Padding (in records) after the per-baseline records of the adjoint, which

@@ -38,11 +38,15 @@ __device__ void prep_slots(const KParams &p, int t);
 // Per-call preparation, one launch.  Rows blockIdx.y < nset: per-source data,
 // (l, m, n - 1), (l/n, m/n), the spectrally scaled Stokes vector per channel
 // (eq. brightness_term) and the Gaussian shape coefficients, one thread per
-// source; each workgroup also records whether one of its sources lies outside
+// source and block of kPrepCh channels (blockIdx.z; with all channels in one
+// thread their exponentials formed a serial chain: 75 sources, 16 channels
+// 9.9 us, 2000 sources, 256 channels 123 us); each workgroup also records whether one of its sources lies outside
 // the domain l^2 + m^2 < 1 of n = sqrt(1 - l^2 - m^2) (Section 2.1, after
 // eq. k_term), whose geometry is then NaN.  Rows nset + t (gradient mode,
 // nc > 0): the adjoint's per-baseline records of timestep t.
 // ---------------------------------------------------------------------------
+constexpr int kPrepCh = 8;
+
 template <class R>
 __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
   using R4 = typename Num<R>::R4;
@@ -57,17 +61,20 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
   const SetDesc sd = p.sets ? p.sets[set] : p.one;
   const int nsrc = sd.npsrc + sd.ngsrc + sd.nxsrc;
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool first = blockIdx.z == 0;
   int outside = 0;
   if (s < nsrc) {
-    const double l = sd.lm[2 * s], m = sd.lm[2 * s + 1];
-    const double r2 = sumsq_rn(l, m);
-    outside = r2 >= 1.0;
-    const double nan = __builtin_nan("");
-    const double n = outside ? nan : sqrt(1.0 - r2);
-    const double nm1 = outside ? nan : -r2 / (1.0 + n);
     const int64_t g = sd.src_off + s;
-    p.src_geo[g] = make_double4(l, m, nm1, outside ? 1.0 : 0.0);
-    p.src_lon[g] = make_double2(l / n, m / n);
+    if (first) {
+      const double l = sd.lm[2 * s], m = sd.lm[2 * s + 1];
+      const double r2 = sumsq_rn(l, m);
+      outside = r2 >= 1.0;
+      const double nan = __builtin_nan("");
+      const double n = outside ? nan : sqrt(1.0 - r2);
+      const double nm1 = outside ? nan : -r2 / (1.0 + n);
+      p.src_geo[g] = make_double4(l, m, nm1, outside ? 1.0 : 0.0);
+      p.src_lon[g] = make_double2(l / n, m / n);
+    }
     const double I = sd.stokes[4 * s], Q = sd.stokes[4 * s + 1];
     const double U = sd.stokes[4 * s + 2], V = sd.stokes[4 * s + 3];
     const double a = sd.alpha[s];
@@ -76,7 +83,8 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
     const int64_t row = p.p64_ns ? 0 : g * p.nchan, step = p.p64_ns ? p.p64_ns : 1;
     R4 *st = static_cast<R4 *>(p.src_st) + row + (p.p64_ns ? s : 0);
     R *sf = static_cast<R *>(p.src_sf) + row + (p.p64_ns ? s : 0);
-    for (int c = 0; c < p.nchan; ++c) {
+    const int c1 = min(p.nchan, static_cast<int>(blockIdx.z + 1) * kPrepCh);
+    for (int c = blockIdx.z * kPrepCh; c < c1; ++c) {
       const double f = exp(a * p.lnfr[c]);
       R4 v;
       v.x = static_cast<R>(f * I);
@@ -87,7 +95,7 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
       if (p.src_f) p.src_f[g * p.nchan + c] = static_cast<float>(f);
       if (p.src_sf) sf[c * step] = static_cast<R>(f);
     }
-    if (s >= sd.npsrc) {
+    if (first && s >= sd.npsrc) {
       // Gaussian or disk shape with the axis ratio folded into the minor-axis
       // pair, so that the quadratic form is A^2 + B^2 with A = du el + dv em
       // and B = du (R em) - dv (R el)
@@ -102,7 +110,7 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
       static_cast<R4 *>(p.src_gs)[g] = v;
     }
   }
-  if (p.dom) {
+  if (p.dom && first) {
     // every workgroup of the set rows writes its flag word (no clearing pass)
     const int any = __syncthreads_or(outside);
     if (threadIdx.x == 0) {
@@ -126,8 +134,8 @@ __device__ void prep_baselines(const KParams &p, int nc, int t) {
   using R4 = typename N::R4;
   const int64_t n = static_cast<int64_t>(p.ntile) * p.nbt;
   R4 *rec = static_cast<R4 *>(const_cast<void *>(p.bl_rec)) + t * n;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * 256) {
+  for (int64_t i = (static_cast<int64_t>(blockIdx.z) * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+       i < n; i += static_cast<int64_t>(gridDim.x) * gridDim.z * 256) {
     const int tile = static_cast<int>(i / p.nbt);
     R4 r;
     r.x = r.y = r.z = R(0);
@@ -154,8 +162,8 @@ __device__ void prep_baselines(const KParams &p, int nc, int t) {
 __device__ void prep_slots(const KParams &p, int t) {
   const int n = p.npair * kPmeBlk * kPmeBlk;
   const double *uvw = p.uvw + static_cast<int64_t>(t) * p.na * 3;
-  for (int i = static_cast<int>(blockIdx.x * 256 + threadIdx.x); i < n;
-       i += static_cast<int>(gridDim.x) * 256) {
+  for (int i = static_cast<int>((blockIdx.z * gridDim.x + blockIdx.x) * 256 + threadIdx.x); i < n;
+       i += static_cast<int>(gridDim.x * gridDim.z) * 256) {
     const int pair = i / (kPmeBlk * kPmeBlk);
     const int2 blk = p.pair_blk[pair];
     const int a = blk.x * kPmeBlk + i / kPmeBlk % kPmeBlk, b = blk.y * kPmeBlk + i % kPmeBlk;
@@ -1084,7 +1092,7 @@ void rime_main(const KParams p) {
   if (MODE != MODE_PREDICT && MODE != MODE_ADJ) {
     const Comp r = block_reduce<NBT>(chi, s_scr);
     if (tid == 0)
-      p.chi2_part[static_cast<int64_t>(set) * p.items_per_set + local_item] =
+      p.chi2_part[static_cast<int64_t>(set) * p.chi2_items + local_item] =
           make_double2(r.s, r.c);
   }
 }
@@ -1092,50 +1100,71 @@ void rime_main(const KParams p) {
 // ---------------------------------------------------------------------------
 // Finalize: deterministic compensated sums of the per-item partials.
 // ---------------------------------------------------------------------------
-// chi^2 of one set from its per-item (sum, compensation) partials, in a fixed
-// order; all 256 threads of the workgroup take part.
-__device__ inline void chi2_reduce(const KParams &p, int set, double2 *scr) {
-  Comp acc;
-  const double2 *part = p.chi2_part + static_cast<int64_t>(set) * p.items_per_set;
-  // each thread merges items tid, tid + 256, ... in that order; four loads are
-  // issued before they are merged
-  int i = threadIdx.x;
-  for (; i + 3 * 256 < p.items_per_set; i += 4 * 256) {
-    double2 v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = part[i + k * 256];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc.merge(v[k].x, v[k].y);
-  }
-  for (; i < p.items_per_set; i += 256) {
-    const double2 v = part[i];
-    acc.merge(v.x, v.y);
-  }
-  const Comp r = block_reduce<256>(acc, scr);
-  if (threadIdx.x == 0) p.chi2_out[set] = r.s + r.c;
-}
-
 __global__ __launch_bounds__(256) void finalize_chi2(const KParams p) {
   __shared__ double2 scr[256 / kWave];
   chi2_reduce(p, blockIdx.x, scr);
 }
 
-// Level 1: grid (source-parameter blocks, item chunks, sets); each thread
-// sums `grad_chunks` consecutive items of one (source, parameter).
-// In gradient mode the grid has one more row of chunks (blockIdx.y ==
-// grad_nchunk) whose first workgroup forms chi^2 instead, which saves a launch.
-__global__ __launch_bounds__(256) void finalize_grad1(const KParams p) {
+// Level 1: workgroups (source-parameter blocks, item chunks, sets); each thread
+// sums `grad_chunks` consecutive items of one (source, parameter).  One launch
+// also forms chi^2 (one workgroup per set, in an extra row of chunks) and, with
+// the matrix-core adjoint, the first level of the point sources' sums, whose
+// rows the others then leave out.
+//
+// Point sources (partials [sr][item][kPmeSR][7]): thread = one column (source,
+// component) of the partial rows, workgroup = 256 contiguous columns of one
+// source range and one chunk of items, so every item row is read as one
+// contiguous 1 KiB run.
+// ---------------------------------------------------------------------------
+constexpr int kPmeFinRow = kPmeSR * 7;
+
+__device__ inline void points_level1(const KParams &p, int bx, int sr, int ch) {
+  const int col = bx * 256 + threadIdx.x;
+  if (col >= min(kPmeSR, p.one.npsrc - sr * kPmeSR) * 7) return;
+  const int64_t nper = static_cast<int64_t>(p.ntime) * p.pme_ncg * p.nblk * p.pme_nqr;
+  const int64_t cs = (nper + p.pme_fchunk - 1) / p.pme_fchunk;
+  const int64_t i1 = min(nper, (ch + 1) * cs);
+  const float *src = p.pgrad + static_cast<int64_t>(sr) * nper * kPmeFinRow + col;
+  Comp acc;
+  int64_t i = ch * cs;
+  for (; i + 4 <= i1; i += 4) {
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = src[(i + k) * kPmeFinRow];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc.add(static_cast<double>(v[k]));
+  }
+  for (; i < i1; ++i) acc.add(static_cast<double>(src[i * kPmeFinRow]));
+  p.pfin[(static_cast<int64_t>(sr) * p.pme_fchunk + ch) * kPmeFinRow + col] =
+      make_double2(acc.s, acc.c);
+}
+
+// First gradient row that level 1 and 2 form from the per-baseline partials.
+__device__ inline int first_row(const KParams &p) { return p.pme_adj ? p.one.npsrc : 0; }
+
+__global__ __launch_bounds__(256) void finalize_grad1(const KParams p, int nblk, int nrow) {
   __shared__ double2 scr[256 / kWave];
-  const int set = blockIdx.z;
-  if (static_cast<int>(blockIdx.y) == p.grad_nchunk) {
-    if (blockIdx.x == 0) chi2_reduce(p, set, scr);
+  const int nmain = nblk * nrow * p.nset;
+  int b = blockIdx.x;
+  if (b >= nmain) {
+    b -= nmain;
+    if (b < p.fin_chi2) {
+      chi2_reduce(p, b, scr);
+    } else {
+      b -= p.fin_chi2;
+      const int bx = b % (kPmeFinRow / 256);
+      b /= kPmeFinRow / 256;
+      points_level1(p, bx, b % p.pme_nsr, b / p.pme_nsr);
+    }
     return;
   }
+  const int bx = b % nblk;
+  b /= nblk;
+  const int chunk = b % nrow, set = b / nrow;
   const SetDesc sd = p.sets ? p.sets[set] : p.one;
   const int nsrc = sd.npsrc + sd.ngsrc + sd.nxsrc;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
+  const int idx = first_row(p) * 10 + bx * 256 + threadIdx.x;
   if (idx >= nsrc * 10) return;
-  const int chunk = blockIdx.y;
   const int i0 = chunk * p.grad_chunks;
   const int i1 = min(p.items_per_set, i0 + p.grad_chunks);
   const int64_t stride = static_cast<int64_t>(nsrc) * 10;
@@ -1156,31 +1185,48 @@ __global__ __launch_bounds__(256) void finalize_grad1(const KParams p) {
   *dst = make_double2(acc.s, acc.c);
 }
 
-// Level 2: one thread per (set, source, parameter) sums the chunks.
-__global__ __launch_bounds__(256) void finalize_grad2(const KParams p) {
-  const int set = blockIdx.y;
-  const SetDesc sd = p.sets ? p.sets[set] : p.one;
-  const int nsrc = sd.npsrc + sd.ngsrc + sd.nxsrc;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= nsrc * 10) return;
-  const int64_t stride = static_cast<int64_t>(nsrc) * 10;
-  const double2 *src = reinterpret_cast<const double2 *>(p.grad_part2) +
-                       sd.src_off * p.grad_nchunk * 10 + idx;
+// Sum of n (sum, compensation) pairs `stride` apart, in order, eight loads at a
+// time.
+__device__ inline double merge_chunks(const double2 *src, int n, int64_t stride) {
   Comp acc;
-  // chunks in order; eight loads are issued before they are merged
   int j = 0;
-  for (; j + 8 <= p.grad_nchunk; j += 8) {
+  for (; j + 8 <= n; j += 8) {
     double2 v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = src[(j + k) * stride];
 #pragma unroll
     for (int k = 0; k < 8; ++k) acc.merge(v[k].x, v[k].y);
   }
-  for (; j < p.grad_nchunk; ++j) {
+  for (; j < n; ++j) {
     const double2 v = src[j * stride];
     acc.merge(v.x, v.y);
   }
-  p.grad_out[sd.src_off * 10 + idx] = 2.0 * (acc.s + acc.c);
+  return 2.0 * (acc.s + acc.c);
+}
+
+// Level 2: one thread per (set, source, parameter) sums the chunks; with the
+// matrix-core adjoint the point sources' rows come from their own chunks
+// (columns 7..9, the shape, are zero).
+__global__ __launch_bounds__(256) void finalize_grad2(const KParams p) {
+  const int set = blockIdx.y;
+  const SetDesc sd = p.sets ? p.sets[set] : p.one;
+  const int nsrc = sd.npsrc + sd.ngsrc + sd.nxsrc;
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= nsrc * 10) return;
+  double out = 0.0;
+  if (idx < first_row(p) * 10) {
+    const int s = idx / 10, j = idx - s * 10;
+    if (j < 7) {
+      const int sr = s / kPmeSR, sl = s % kPmeSR;
+      out = merge_chunks(p.pfin + static_cast<int64_t>(sr) * p.pme_fchunk * kPmeFinRow + sl * 7 + j,
+                         p.pme_fchunk, kPmeFinRow);
+    }
+  } else {
+    out = merge_chunks(reinterpret_cast<const double2 *>(p.grad_part2) +
+                           sd.src_off * p.grad_nchunk * 10 + idx,
+                       p.grad_nchunk, static_cast<int64_t>(nsrc) * 10);
+  }
+  p.grad_out[sd.src_off * 10 + idx] = out;
 }
 
 // ---------------------------------------------------------------------------
@@ -1200,10 +1246,27 @@ __global__ __launch_bounds__(256) void die_grad(const KParams p) {
   const int a = static_cast<int>(rest % p.na);
   const int t = static_cast<int>(rest / p.na);
   Comp re, im;
-  for (int j = p.ant_off[a]; j < p.ant_off[a + 1]; ++j) {
+  // eight loads are issued before they are added (50 antennas, 21 timesteps, 37
+  // channels, one at a time: 58 us)
+  const double2 *part = p.die_part + (static_cast<int64_t>(t) * p.nbl * p.nchan + c) * 8 + k;
+  const int j1 = p.ant_off[a + 1];
+  int j = p.ant_off[a];
+  for (; j + 8 <= j1; j += 8) {
+    double2 v[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      const int2 e = p.ant_bl[j + x];
+      v[x] = part[static_cast<int64_t>(e.x) * p.nchan * 8 + e.y * 4];
+    }
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+      re.add(v[x].x);
+      im.add(v[x].y);
+    }
+  }
+  for (; j < j1; ++j) {
     const int2 e = p.ant_bl[j];
-    const double2 v =
-        p.die_part[((static_cast<int64_t>(t) * p.nbl + e.x) * p.nchan + c) * 8 + e.y * 4 + k];
+    const double2 v = part[static_cast<int64_t>(e.x) * p.nchan * 8 + e.y * 4];
     re.add(v.x);
     im.add(v.y);
   }
@@ -1222,6 +1285,18 @@ __global__ __launch_bounds__(256) void stokes_t_grad(const KParams p) {
   const int tc = t / p.tchunk, tt = t - tc * p.tchunk;
   const int s = static_cast<int>(sk / 4), k = static_cast<int>(sk % 4);
   Comp acc;
+  // adds the n items x(0), x(1), ..., eight loads at a time
+  auto sum = [&](int64_t n, auto x) {
+    int64_t i = 0;
+    for (; i + 8 <= n; i += 8) {
+      double v[8];
+#pragma unroll
+      for (int y = 0; y < 8; ++y) v[y] = x(i + y);
+#pragma unroll
+      for (int y = 0; y < 8; ++y) acc.add(v[y]);
+    }
+    for (; i < n; ++i) acc.add(x(i));
+  };
   if (p.pme_adj && s < p.one.npsrc) {
     // point sources with the matrix-core adjoint: its per-item partials of
     // timestep t, columns 2..5 (the Stokes sums times the spectral factor)
@@ -1229,13 +1304,13 @@ __global__ __launch_bounds__(256) void stokes_t_grad(const KParams p) {
     const int64_t nit = static_cast<int64_t>(p.pme_ncg) * p.nblk * p.pme_nqr;
     const float *src =
         p.pgrad + (static_cast<int64_t>(sr) * p.ntime + t) * nit * (kPmeSR * 7) + sl * 7 + 2 + k;
-    for (int64_t i = 0; i < nit; ++i) acc.add(static_cast<double>(src[i * (kPmeSR * 7)]));
+    sum(nit, [&](int64_t i) { return static_cast<double>(src[i * (kPmeSR * 7)]); });
   } else {
-    for (int chb = 0; chb < p.nchb; ++chb)
-      for (int tile = 0; tile < p.ntile; ++tile) {
-        const int64_t item = tile + static_cast<int64_t>(p.ntile) * (chb + p.nchb * tc);
-        acc.add(p.gst_part[(item * p.tchunk + tt) * nsrc * 4 + sk]);
-      }
+    // channel blocks, then tiles: consecutive items of the time chunk
+    const int64_t item0 = static_cast<int64_t>(p.ntile) * p.nchb * tc;
+    const double *src = p.gst_part + (item0 * p.tchunk + tt) * nsrc * 4 + sk;
+    const int64_t step = static_cast<int64_t>(p.tchunk) * nsrc * 4;
+    sum(static_cast<int64_t>(p.ntile) * p.nchb, [&](int64_t i) { return src[i * step]; });
   }
   p.grad_stokes_t[idx] = 2.0 * (acc.s + acc.c);
 }
@@ -1317,7 +1392,7 @@ hipError_t launch_prep(const KParams &p, bool fp64, int max_nsrc, int rec_nc,
   // per timestep after the per-set rows); one workgroup per set row at least,
   // which writes the set's domain flag also for a sky without sources
   const int nblk = max_nsrc > 0 ? (max_nsrc + 255) / 256 : 1;
-  dim3 grid(nblk, p.nset + (rec_nc > 0 ? p.ntime : 0));
+  const dim3 grid(nblk, p.nset + (rec_nc > 0 ? p.ntime : 0), (p.nchan + kPrepCh - 1) / kPrepCh);
   if (fp64)
     hipLaunchKernelGGL(prep_sources<double>, grid, dim3(256), 0, stream, p, rec_nc);
   else
@@ -1339,13 +1414,19 @@ hipError_t launch_finalize(const KParams &p, int mode, int max_nsrc, hipStream_t
     hipLaunchKernelGGL(finalize_chi2, dim3(p.nset), dim3(256), 0, stream, p);
     return hipGetLastError();
   }
-  // level 1 of the gradient, plus chi^2 in the extra row of chunks
-  const int nblk = (max_nsrc * 10 + 255) / 256;
-  hipLaunchKernelGGL(finalize_grad1, dim3(nblk, p.grad_nchunk + (with_chi2 ? 1 : 0), p.nset),
-                     dim3(256), 0, stream, p);
+  KParams q = p;
+  q.fin_chi2 = with_chi2 ? p.nset : 0;
+  const int ext = max_nsrc - (p.pme_adj ? p.one.npsrc : 0);  // rows of the per-baseline partials
+  const int nblk = (ext * 10 + 255) / 256;
+  const int points = p.pme_adj ? kPmeFinRow / 256 * p.pme_nsr * p.pme_fchunk : 0;
+  const int grid = nblk * p.grad_nchunk * p.nset + q.fin_chi2 + points;
+  if (grid > 0)
+    hipLaunchKernelGGL(finalize_grad1, dim3(grid), dim3(256), 0, stream, q, max(nblk, 1),
+                       nblk > 0 ? p.grad_nchunk : 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(finalize_grad2, dim3(nblk, p.nset), dim3(256), 0, stream, p);
+  hipLaunchKernelGGL(finalize_grad2, dim3((max_nsrc * 10 + 255) / 256, p.nset), dim3(256), 0, stream,
+                     q);
   return hipGetLastError();
 }
 

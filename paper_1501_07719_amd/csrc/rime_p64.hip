@@ -645,9 +645,15 @@ __global__ __launch_bounds__(256, 2) void p64_adjoint(const KParams p) {
 // Gradient rows from the adjoint partials, in two passes with a fixed order:
 // thread = one column (parameter, source) of a chunk of items, then thread =
 // (source, parameter) over the chunks.
+// The first launch also forms chi^2, in an extra row of workgroups.
 __global__ __launch_bounds__(256) void p64_fin_items(const KParams p) {
   constexpr int kRow = 10 * kWave;
+  __shared__ double2 scr[256 / kWave];
   const int sg = blockIdx.y, ch = blockIdx.z;
+  if (sg == p.p64_nsg) {
+    if (blockIdx.x == 0 && ch == 0) chi2_reduce(p, 0, scr);
+    return;
+  }
   const int col = blockIdx.x * 256 + threadIdx.x;
   if (col >= kRow) return;
   const int64_t nper = static_cast<int64_t>(p.ntime) * p.p64_ncg * p.nsub * p.p64_split;
@@ -704,7 +710,15 @@ __global__ __launch_bounds__(256) void p64_stokes_t(const KParams p) {
                       (static_cast<int64_t>(blockIdx.y) * p.ntime + t) * nit * (10 * kWave) +
                       (2 + k) * kWave + s;
   Comp acc;
-  for (int i = 0; i < nit; ++i) acc.add(src[static_cast<int64_t>(i) * (10 * kWave)]);
+  int i = 0;
+  for (; i + 8 <= nit; i += 8) {
+    double v[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = src[static_cast<int64_t>(i + x) * (10 * kWave)];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) acc.add(v[x]);
+  }
+  for (; i < nit; ++i) acc.add(src[static_cast<int64_t>(i) * (10 * kWave)]);
   const int nsrc = p.one.npsrc + p.one.ngsrc + p.one.nxsrc;
   p.grad_stokes_t[(static_cast<int64_t>(t) * nsrc + tl.s0 + s) * 4 + k] = 2.0 * (acc.s + acc.c);
 }
@@ -773,7 +787,7 @@ hipError_t launch_p64_adjoint(const KParams &p, hipStream_t stream) {
 }
 
 hipError_t launch_p64_finalize(const KParams &p, hipStream_t stream) {
-  const dim3 g1((10 * kWave + 255) / 256, static_cast<unsigned>(p.p64_nsg),
+  const dim3 g1((10 * kWave + 255) / 256, static_cast<unsigned>(p.p64_nsg + 1),
                 static_cast<unsigned>(p.pme_fchunk));
   hipLaunchKernelGGL(p64_fin_items, g1, dim3(256), 0, stream, p);
   hipError_t e = hipGetLastError();

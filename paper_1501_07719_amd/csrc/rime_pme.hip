@@ -12,8 +12,8 @@
 //                (22 significant bits; the phase argument is formed and
 //                reduced in float64 as in the float32 per-baseline kernels),
 //                and the beam's d ln e / d(l, m) factor;
-//   pme_scale    per (channel, Stokes parameter) power-of-two scale of the
-//                source-side operand;
+//                and per (channel, Stokes parameter) the power-of-two scale of
+//                the forward's source-side operand (pme_scale);
 //   pme_forward  one Q block of 32 antennas against one or two P blocks per
 //                workgroup, one Stokes parameter per wavefront: the real form
 //                of the product over (s, re/im) with v_mfma_f32_32x32x16_f16,
@@ -25,8 +25,8 @@
 //   pme_mfrag    the residual matrices of the adjoint as fp16 MFMA fragments;
 //   pme_adjoint  the gradient of chi^2 with respect to the point-source
 //                parameters (see the comment there);
-//   pme_fin_items, pme_finalize
-//                float64 sums of the adjoint's per-workgroup partials.
+//                (its per-workgroup partials are summed in float64 by
+//                finalize_grad1 and finalize_grad2).
 // Operand fragments follow the gfx950 lane layout of the 32x32x16 fp16
 // instruction: A[i][k] in lane i + 32 (k / 8), element k % 8; B[k][j] in lane
 // j + 32 (k / 8), element k % 8; D[i][j] in lane j + 32 ((i / 4) % 2),
@@ -91,6 +91,54 @@ __device__ inline half8 rot8(half8 v) {
   return r;
 }
 
+// St'_k (k = I, Q, U, V) of source s of the set at channel c and timestep t:
+// the spectrally scaled Stokes vector, or, with brightness per timestep (ST),
+// the spectral factor times that timestep's Stokes vector (rounded as in the
+// per-baseline kernels).  The kernels that call it per chunk take ST as a
+// template parameter, so that the plain calls do not carry its registers.
+template <bool ST>
+__device__ inline float4 pme_stokes(const KParams &p, int s, int c, int t) {
+  const int64_t gs = p.one.src_off + s;
+  if (ST) {
+    const int nsrc = p.one.npsrc + p.one.ngsrc + p.one.nxsrc;
+    const double *q = p.stokes_t + (static_cast<int64_t>(t) * nsrc + s) * 4;
+    const double f = static_cast<double>(static_cast<const float *>(p.src_sf)[gs * p.nchan + c]);
+    return make_float4(static_cast<float>(f * q[0]), static_cast<float>(f * q[1]),
+                       static_cast<float>(f * q[2]), static_cast<float>(f * q[3]));
+  }
+  return static_cast<const float4 *>(p.src_st)[gs * p.nchan + c];
+}
+
+// Forward scale of channel c: exponent e of max_s |St'_k,s(nu)| (over the
+// timesteps too with brightness per timestep), by one workgroup.
+__device__ inline void pme_scale(const KParams &p, int c, float (*s_m)[256 / kWave]) {
+  const SetDesc sd = p.one;
+  const int nt = p.stokes_t ? p.ntime : 1;
+  float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int t = 0; t < nt; ++t)
+    for (int s = threadIdx.x; s < sd.npsrc; s += 256) {
+      const float4 v = p.stokes_t ? pme_stokes<true>(p, s, c, t) : pme_stokes<false>(p, s, c, t);
+      m[0] = fmaxf(m[0], fabsf(v.x));
+      m[1] = fmaxf(m[1], fabsf(v.y));
+      m[2] = fmaxf(m[2], fabsf(v.z));
+      m[3] = fmaxf(m[3], fabsf(v.w));
+    }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) m[k] = fmaxf(m[k], __shfl_xor(m[k], off, kWave));
+    if (threadIdx.x % kWave == 0) s_m[k][threadIdx.x / kWave] = m[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const int k = threadIdx.x;
+    const float mm = fmaxf(fmaxf(s_m[k][0], s_m[k][1]), fmaxf(s_m[k][2], s_m[k][3]));
+    int e = 0;
+    if (mm > 0.0f) frexpf(mm, &e);
+    p.pme_exp[c * 4 + k] = e;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Phase planes: thread = (source, antenna) of one timestep and one block of
 // p.phase_nc channels, reusing the float64 phase argument tau and the beam
@@ -101,8 +149,17 @@ __device__ inline half8 rot8(half8 v) {
 
 __global__ __launch_bounds__(256) void pme_phase(const KParams p) {
   using N = Num<float>;
+  __shared__ float s_m[4][256 / kWave];
   const SetDesc sd = p.one;
   const int tt = blockIdx.y;
+  if (tt >= p.pme_nt) {
+    // the extra row of workgroups: the forward's scales
+    for (int c = blockIdx.z * gridDim.x + blockIdx.x; c < p.nchan; c += gridDim.x * gridDim.z) {
+      pme_scale(p, c, s_m);
+      __syncthreads();
+    }
+    return;
+  }
   const int t = p.pme_t0 + tt;
   const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int nap = p.nap;
@@ -157,58 +214,6 @@ __global__ __launch_bounds__(256) void pme_phase(const KParams p) {
     hi[c * plane] = pack_h2(rh, ih);
     lo[c * plane] = pack_h2(rl, il);
     if (k3p) k3p[c * plane] = k3;
-  }
-}
-
-// St'_k (k = I, Q, U, V) of source s of the set at channel c and timestep t:
-// the spectrally scaled Stokes vector, or, with brightness per timestep (ST),
-// the spectral factor times that timestep's Stokes vector (rounded as in the
-// per-baseline kernels).  The kernels that call it per chunk take ST as a
-// template parameter, so that the plain calls do not carry its registers.
-template <bool ST>
-__device__ inline float4 pme_stokes(const KParams &p, int s, int c, int t) {
-  const int64_t gs = p.one.src_off + s;
-  if (ST) {
-    const int nsrc = p.one.npsrc + p.one.ngsrc + p.one.nxsrc;
-    const double *q = p.stokes_t + (static_cast<int64_t>(t) * nsrc + s) * 4;
-    const double f = static_cast<double>(static_cast<const float *>(p.src_sf)[gs * p.nchan + c]);
-    return make_float4(static_cast<float>(f * q[0]), static_cast<float>(f * q[1]),
-                       static_cast<float>(f * q[2]), static_cast<float>(f * q[3]));
-  }
-  return static_cast<const float4 *>(p.src_st)[gs * p.nchan + c];
-}
-
-// ---------------------------------------------------------------------------
-// Forward scale: exponent e of max_s |St'_k,s(nu)| (over the timesteps too with
-// brightness per timestep), one workgroup per channel.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void pme_scale(const KParams p) {
-  __shared__ float s_m[4][256 / kWave];
-  const int c = blockIdx.x;
-  const SetDesc sd = p.one;
-  const int nt = p.stokes_t ? p.ntime : 1;
-  float m[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  for (int t = 0; t < nt; ++t)
-    for (int s = threadIdx.x; s < sd.npsrc; s += 256) {
-      const float4 v = p.stokes_t ? pme_stokes<true>(p, s, c, t) : pme_stokes<false>(p, s, c, t);
-      m[0] = fmaxf(m[0], fabsf(v.x));
-      m[1] = fmaxf(m[1], fabsf(v.y));
-      m[2] = fmaxf(m[2], fabsf(v.z));
-      m[3] = fmaxf(m[3], fabsf(v.w));
-    }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) m[k] = fmaxf(m[k], __shfl_xor(m[k], off, kWave));
-    if (threadIdx.x % kWave == 0) s_m[k][threadIdx.x / kWave] = m[k];
-  }
-  __syncthreads();
-  if (threadIdx.x < 4) {
-    const int k = threadIdx.x;
-    const float mm = fmaxf(fmaxf(s_m[k][0], s_m[k][1]), fmaxf(s_m[k][2], s_m[k][3]));
-    int e = 0;
-    if (mm > 0.0f) frexpf(mm, &e);
-    p.pme_exp[c * 4 + k] = e;
   }
 }
 
@@ -785,57 +790,11 @@ __global__ __launch_bounds__(256, 2) void pme_adjoint(const KParams p) {
   for (int i = tid; i < (send - sbeg) * 7; i += 256) dst[i] = (&s_acc[0][0])[i];
 }
 
-// Point-source gradient rows from the adjoint partials, in two float64 passes
-// with a fixed order.  pme_fin_items: thread = one column (source, component)
-// of the partial rows, workgroup = 256 contiguous columns of one source range
-// and one chunk of items, so every item row is read as one contiguous 1 KiB
-// run.  pme_finalize: thread = (source, gradient column), summing the chunks;
-// columns 7..9 (shape) are zero.
-__global__ __launch_bounds__(256) void pme_fin_items(const KParams p) {
-  constexpr int kRow = kPmeSR * 7;
-  const int sr = blockIdx.y, ch = blockIdx.z;
-  const int col = blockIdx.x * 256 + threadIdx.x;
-  if (col >= min(kPmeSR, p.one.npsrc - sr * kPmeSR) * 7) return;
-  const int64_t nper = static_cast<int64_t>(p.ntime) * p.pme_ncg * p.nblk * p.pme_nqr;
-  const int64_t cs = (nper + p.pme_fchunk - 1) / p.pme_fchunk;
-  const int64_t i1 = min(nper, (ch + 1) * cs);
-  const float *src = p.pgrad + static_cast<int64_t>(sr) * nper * kRow + col;
-  Comp acc;
-  int64_t i = ch * cs;
-  for (; i + 4 <= i1; i += 4) {
-    float v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = src[(i + k) * kRow];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) acc.add(static_cast<double>(v[k]));
-  }
-  for (; i < i1; ++i) acc.add(static_cast<double>(src[i * kRow]));
-  p.pfin[(static_cast<int64_t>(sr) * p.pme_fchunk + ch) * kRow + col] = make_double2(acc.s, acc.c);
-}
-
-__global__ __launch_bounds__(256) void pme_finalize(const KParams p) {
-  constexpr int kRow = kPmeSR * 7;
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= static_cast<int64_t>(p.one.npsrc) * 10) return;
-  const int s = static_cast<int>(idx / 10), j = static_cast<int>(idx % 10);
-  double out = 0.0;
-  if (j < 7) {
-    const int sr = s / kPmeSR, sl = s % kPmeSR;
-    const double2 *src = p.pfin + static_cast<int64_t>(sr) * p.pme_fchunk * kRow + sl * 7 + j;
-    Comp r;
-    for (int ch = 0; ch < p.pme_fchunk; ++ch) {
-      const double2 v = src[static_cast<int64_t>(ch) * kRow];
-      r.merge(v.x, v.y);
-    }
-    out = 2.0 * (r.s + r.c);
-  }
-  p.grad_out[p.one.src_off * 10 + idx] = out;
-}
-
 // ---------------------------------------------------------------------------
 // Launchers (timesteps [p.pme_t0, p.pme_t0 + p.pme_nt))
 // ---------------------------------------------------------------------------
-static hipError_t launch_phase(const KParams &p, hipStream_t stream) {
+// scale: also the scales of the forward (an extra row of workgroups).
+static hipError_t launch_phase(const KParams &p, bool scale, hipStream_t stream) {
   const int64_t plane = static_cast<int64_t>(p.one.npsrc) * p.nap;
   // channels per workgroup, as measured.  Planes of 1 MiB and more write
   // fastest in blocks of 4 channels: for 1500 sources x 224 antennas, 20
@@ -844,21 +803,16 @@ static hipError_t launch_phase(const KParams &p, hipStream_t stream) {
   // for 1000 x 64, 100 timesteps and 64 channels, 0.61 ms against 0.70 ms.
   KParams q = p;
   q.phase_nc = plane * static_cast<int64_t>(sizeof(uint32_t)) >= (int64_t(1) << 20) ? 4 : 16;
-  dim3 g1(static_cast<unsigned>((plane + 255) / 256), static_cast<unsigned>(p.pme_nt),
+  dim3 g1(static_cast<unsigned>((plane + 255) / 256),
+          static_cast<unsigned>(p.pme_nt + (scale ? 1 : 0)),
           static_cast<unsigned>((p.nchan + q.phase_nc - 1) / q.phase_nc));
   hipLaunchKernelGGL(pme_phase, g1, dim3(256), 0, stream, q);
   return hipGetLastError();
 }
 
-hipError_t launch_pme_scale(const KParams &p, hipStream_t stream) {
-  if (p.one.npsrc <= 0) return hipSuccess;
-  hipLaunchKernelGGL(pme_scale, dim3(p.nchan), dim3(256), 0, stream, p);
-  return hipGetLastError();
-}
-
 hipError_t launch_pme(const KParams &p, hipStream_t stream) {
   if (p.one.npsrc <= 0 || p.pme_nt <= 0) return hipSuccess;
-  hipError_t e = launch_phase(p, stream);
+  hipError_t e = launch_phase(p, p.pme_t0 == 0, stream);
   if (e != hipSuccess) return e;
   const int64_t nitems = static_cast<int64_t>(p.pme_nt) * p.nchan * p.ngroup;
   const int64_t grid = 8 * ((nitems + 7) / 8);
@@ -879,7 +833,7 @@ hipError_t launch_pme(const KParams &p, hipStream_t stream) {
 
 hipError_t launch_pme_adjoint(const KParams &p, bool phase, hipStream_t stream) {
   if (p.one.npsrc <= 0 || p.pme_nt <= 0) return hipSuccess;
-  hipError_t e = phase ? launch_phase(p, stream) : hipSuccess;
+  hipError_t e = phase ? launch_phase(p, false, stream) : hipSuccess;
   if (e != hipSuccess) return e;
   const int64_t nfrag = static_cast<int64_t>(p.pme_nt) * p.nchan * p.nblk * p.pme_nqr;
   hipLaunchKernelGGL(pme_mfrag, dim3(static_cast<unsigned>(nfrag)), dim3(256), 0, stream, p);
@@ -893,19 +847,6 @@ hipError_t launch_pme_adjoint(const KParams &p, bool phase, hipStream_t stream) 
   else
     hipLaunchKernelGGL(pme_adjoint<false>, dim3(static_cast<unsigned>(grid)), dim3(256), 0,
                        stream, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_pme_finalize(const KParams &p, hipStream_t stream) {
-  if (p.one.npsrc <= 0) return hipSuccess;
-  const dim3 g1(kPmeSR * 7 / 256, static_cast<unsigned>(p.pme_nsr),
-                static_cast<unsigned>(p.pme_fchunk));
-  hipLaunchKernelGGL(pme_fin_items, g1, dim3(256), 0, stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t n = static_cast<int64_t>(p.one.npsrc) * 10;
-  hipLaunchKernelGGL(pme_finalize, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0,
-                     stream, p);
   return hipGetLastError();
 }
 
