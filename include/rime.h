@@ -282,7 +282,8 @@ void rime_batch_destroy(rime_batch *batch);
  * the order the sets were given.  With use_graph != 0 the launch sequence is
  * captured into a hipGraph on the first call for a given (data, weight, chi2,
  * grad, ws, stream, precision) and replayed afterwards.  With a matrix-core
- * variant the sets alternate between `stream` and a stream that
+ * variant, and with float64 arithmetic where the sets are large enough to run
+ * one by one, the sets alternate between `stream` and a stream that
  * rime_batch_create makes (default priority, destroyed with the batch); it is
  * forked from and joined back to `stream` by events, so all work of the call
  * is ordered after earlier work on `stream` and before later work on it,

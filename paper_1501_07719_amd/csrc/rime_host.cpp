@@ -1801,15 +1801,30 @@ static int64_t batch_dom_words(const rime_batch *b) {
   return n;
 }
 
-// Workspace of one batched call with variant vidx: a matrix-core variant runs
-// the single-sky pipeline once per set, after a header of domain flags, with
-// one set's layout per lane (each reused in stream order); the others run
-// all sets in one launch sequence.
-static size_t batch_ws(const rime_batch *b, int mode, int prec, int vidx, int fidx,
+// Whether a batched float64 forward or gradient (or float64-residual chi^2)
+// pays to run set by set on the float64 engine: sets of 2^25 (antenna pair,
+// timestep, channel, source) terms and more on average.  Smaller ones keep the
+// one launch sequence for all sets, whose launches are shared (gradient, one
+// sequence against set by set: 8 sets of 1.2e7 terms 670 against 851 us, 16 of
+// 3.6e7 4.52 against 4.20 ms, 8 of 6.5e7 2.33 against 1.93 ms, 16 of 8.8e7
+// 9.9 against 7.4 ms).
+static bool batch_engine(const rime_batch *b, int mode, int prec, const Variant &v) {
+  const rime_plan *plan = b->plan;
+  const int64_t n = b->total_src / b->nset;
+  return b->nset > 1 && (prec == RIME_FP64 || (prec == kRes64 && mode == RIME_MODE_CHI2)) &&
+         p64_active(plan, v, RIME_FP64, 1, n) &&
+         static_cast<double>(plan->ntime) * plan->nbl * plan->nchan * static_cast<double>(n) >=
+             double(1 << 25);
+}
+
+// Workspace of one batched call with variant vidx.  per_set: the single-sky
+// pipeline once per set, after a header of domain flags, with one set's layout
+// per lane (each reused in stream order); else all sets in one launch
+// sequence.
+static size_t batch_ws(const rime_batch *b, int mode, int prec, int vidx, int fidx, bool per_set,
                        bool lean = false) {
-  const Variant *v = variant_info(mode, prec, vidx);
-  if (!v) return 0;
-  if (per_set_variant(b->plan, mode, prec, *v))
+  if (!variant_info(mode, prec, vidx)) return 0;
+  if (per_set)
     return align_up(static_cast<size_t>(batch_dom_words(b)) * sizeof(int32_t)) +
            batch_lanes(b) *
                align_up(call_ws(b->plan, mode, prec, vidx, fidx, 1, b->max_nsrc, 0, lean));
@@ -1827,7 +1842,12 @@ size_t rime_batch_workspace_size(const rime_batch *b, rime_mode mode, rime_preci
                      ? variant_count(RIME_MODE_CHI2, kRes64)
                      : 1;
   for (int i = 0; i < variant_count(mode, prec); ++i)
-    for (int f = 0; f < nf; ++f) best = std::max(best, batch_ws(b, mode, prec, i, f));
+    for (int f = 0; f < nf; ++f) {
+      const Variant &v = *variant_info(mode, prec, i);
+      const bool per_set = per_set_variant(b->plan, mode, prec, v);
+      best = std::max(best, batch_ws(b, mode, prec, i, f, per_set));
+      if (batch_engine(b, mode, prec, v)) best = std::max(best, batch_ws(b, mode, prec, i, f, true));
+    }
   return best;
 }
 
@@ -1842,10 +1862,13 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
   const int fidx = plan->variant[RIME_MODE_CHI2][prec];
   const Variant *v = variant_info(mode, prec, vidx);
   if (!v) return RIME_ERR_UNSUPPORTED;
-  const bool lean = ws_bytes < batch_ws(b, mode, prec, vidx, fidx);
-  if (!ws || ws_bytes < batch_ws(b, mode, prec, vidx, fidx, lean)) return RIME_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool per_set = per_set_variant(plan, mode, prec, *v);
+  const bool per_set = per_set_variant(plan, mode, prec, *v) ||
+                       (batch_engine(b, mode, prec, *v) &&
+                        ws_bytes >= batch_ws(b, mode, prec, vidx, fidx, true));
+  const bool lean = ws_bytes < batch_ws(b, mode, prec, vidx, fidx, per_set);
+  if (!ws || ws_bytes < batch_ws(b, mode, prec, vidx, fidx, per_set, lean))
+    return RIME_ERR_WORKSPACE;
   const int lanes = per_set ? batch_lanes(b) : 1;
   Call base;
   base.mode = mode;
@@ -1864,10 +1887,10 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
       c.grad = grad;
       return enqueue(plan, c, vidx, ws, ws_bytes, s);
     }
-    // matrix-core variant: the single-sky pipeline per set, set i in lane
-    // i % lanes with that lane's part of the workspace (after the batch's
-    // domain header); the timing events (if any) bracket the whole sequence
-    // on the caller's stream
+    // matrix-core variant or float64 engine: the single-sky pipeline per set,
+    // set i in lane i % lanes with that lane's part of the workspace (after
+    // the batch's domain header); the timing events (if any) bracket the whole
+    // sequence on the caller's stream
     const size_t hdr = align_up(static_cast<size_t>(batch_dom_words(b)) * sizeof(int32_t));
     const size_t lane_bytes =
         align_up(call_ws(plan, mode, prec, vidx, fidx, 1, b->max_nsrc, 0, lean));

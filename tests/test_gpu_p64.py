@@ -98,6 +98,39 @@ def test_engine_equals_per_baseline_kernel(na, ntime, nchan, npsrc, ng, nx, kind
     check(run(obs, sky, D, W, 1), run(obs, sky, D, W, 0), obs, sky)
 
 
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_by_sets_equals_one_sequence(graph):
+    """Sets large enough to run one by one on the engine, against the launch
+    sequence over all sets (a workspace too small for the planes)."""
+    obs, sky, D, W = problem(64, 12, 45, 64, 64, 0, "")
+    plan = R.Plan(obs)
+    skies = [R.DeviceSky.from_host(sky.subset(n, m)) for n, m in ((64, 64), (64, 40), (50, 63))]
+    batch = R.Batch(plan, skies)
+    Dd, Wd = torch.as_tensor(D, device="cuda"), torch.as_tensor(W, device="cuda")
+    full = batch.workspace_size(R.MODE_CHI2_GRAD, R.FP64)
+    base = R.rime_workspace_size(plan, R.MODE_CHI2_GRAD, R.FP64, 3, batch.total_src)
+    assert base < full
+    out = []
+    with torch.cuda.stream(torch.cuda.Stream()):
+        for n in (full, base):
+            ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+            chi2 = torch.full((3,), float("nan"), dtype=torch.float64, device="cuda")
+            grad = torch.full((batch.total_src, 10), float("nan"), dtype=torch.float64, device="cuda")
+            for _ in range(3):
+                R.rime_chi2_batched(batch, R.FP64, Dd, Wd, chi2, grad, ws, use_graph=graph)
+            torch.cuda.current_stream().synchronize()
+            assert R.rime_domain_status(ws) == 0
+            out.append((chi2.cpu().numpy(), grad.cpu().numpy()))
+    assert np.abs(out[0][0] / out[1][0] - 1).max() <= TOL[0]
+    at = 0
+    for s in skies:
+        a, b = (o[1][at:at + s.nsrc] for o in out)
+        assert max(grad_errors(a, b, s.npsrc).values()) <= TOL[0]
+        at += s.nsrc
+    batch.close()
+    plan.close()
+
+
 def test_engine_terms():
     obs, sky, D, W = problem(18, 3, 5, 70, 50, 40, "")
     rng = np.random.default_rng(5)
