@@ -352,19 +352,6 @@ bool pme_active(const Variant &v, int prec, int nset) {
   return v.pme && prec != RIME_FP64 && nset == 1;
 }
 
-// The float64 engine (rime_p64.hip) runs the float64 forward and gradient of
-// single-sky calls with the default variant's shape (256 threads, two
-// channels per thread) on arrays of more than 96 baselines, none of them twice
-// (an antenna-pair slot holds one), for skies of 32 sources and more: below, a
-// launch more costs what the shorter loops save (46 antennas, 4 (timestep,
-// channel), predict: 40 sources 17.4 against 21.4 us, 8 sources 14.3 against
-// 12.1).  The other calls, and calls whose workspace does not hold its planes,
-// run on the per-baseline kernel.
-bool p64_active(const rime_plan *plan, const Variant &v, int prec, int nset, int64_t total_src) {
-  return prec == RIME_FP64 && nset == 1 && v.threads == 256 && v.nc == 2 &&
-         plan->nbl > 96 && plan->pme_adj_ok && total_src >= 32;
-}
-
 // Whether a call on such a plan takes the engine for its sky: a gradient only
 // when at least half of the lanes of its groups of 64 sources of one
 // morphology hold a source (46 antennas, 1600 (timestep, channel), 28 points +
@@ -385,6 +372,7 @@ struct P64Geometry {
   bool k3 = false;         // planes of the beam-gradient factor
   size_t plane_t = 0;      // plane entries per timestep
   size_t rho_t = 0;        // residual slots x 4 per timestep
+  size_t per_t = 0;        // bytes of both
   int tpass = 1;           // timesteps per pass
   int nr = 4, ntask = 0;   // forward: baselines per lane, tasks
   int tch = 1;             // forward: timesteps per work item
@@ -402,10 +390,10 @@ P64Geometry p64_geometry(const rime_plan *plan, int mode, int64_t total_src) {
   g.ns = static_cast<int>((total_src + 7) / 8 * 8);
   g.plane_t = static_cast<size_t>(plan->nchan) * g.ns * g.nap;
   g.rho_t = grad ? static_cast<size_t>(plan->nchan) * plan->npair * kPmeBlk * kPmeBlk * 4 : 0;
-  const size_t per_t = g.plane_t * (sizeof(double2) + (g.k3 ? sizeof(double) : 0)) +
-                       g.rho_t * sizeof(double2);
+  g.per_t = g.plane_t * (sizeof(double2) + (g.k3 ? sizeof(double) : 0)) +
+            g.rho_t * sizeof(double2);
   g.tpass = static_cast<int>(
-      std::max<size_t>(1, std::min<size_t>(plan->ntime, kP64PassBytes / per_t)));
+      std::max<size_t>(1, std::min<size_t>(plan->ntime, kP64PassBytes / g.per_t)));
   // four baselines per lane once that gives the chip's 1024 SIMDs two
   // wavefronts each; one per lane below (shorter chains on an idle chip)
   const int64_t w4 = static_cast<int64_t>(plan->ntime) * plan->nchan * plan->ntask4;
@@ -431,6 +419,38 @@ P64Geometry p64_geometry(const rime_plan *plan, int mode, int64_t total_src) {
   return g;
 }
 
+// Bytes of the adjoint's partial gradients: 10 doubles per lane of each item.
+size_t p64_part_bytes(const rime_plan *plan, const P64Geometry &g, int mode) {
+  if (mode != RIME_MODE_CHI2_GRAD) return 0;
+  return static_cast<size_t>(g.nsg_max) * plan->ntime * g.ncg * plan->nsub * g.split * 10 * kWave *
+         sizeof(double);
+}
+
+// The float64 engine (rime_p64.hip) runs the float64 forward and gradient of
+// single-sky calls with the default variant's shape (256 threads, two
+// channels per thread) on arrays of more than 96 baselines, none of them twice
+// (an antenna-pair slot holds one), for skies of 32 sources and more: below, a
+// launch more costs what the shorter loops save (46 antennas, 4 (timestep,
+// channel), predict: 40 sources 17.4 against 21.4 us, 8 sources 14.3 against
+// 12.1).  The other calls, and calls whose workspace does not hold its planes,
+// run on the per-baseline kernel.
+//
+// A workspace must also stay near what the per-baseline kernel asks for, and
+// the grids within their limits: one timestep's planes and residuals and the
+// partial gradients take at most one pass's bound each, and the planes' and
+// the sums' grid rows (timesteps, channels in fours, groups of 64 sources)
+// stay under 2^16.
+bool p64_active(const rime_plan *plan, const Variant &v, int prec, int nset, int64_t total_src,
+                int mode) {
+  if (prec != RIME_FP64 || nset != 1 || v.threads != 256 || v.nc != 2 || plan->nbl <= 96 ||
+      !plan->pme_adj_ok || total_src < 32)
+    return false;
+  if (plan->ntime > (1 << 15) || plan->nchan > (1 << 17) || total_src > (1 << 21)) return false;
+  const P64Geometry g = p64_geometry(plan, mode, total_src);
+  return g.per_t <= kP64PassBytes && p64_part_bytes(plan, g, mode) <= kP64PassBytes;
+}
+
+
 // Chunks of adjoint items that the first pass of the engine's gradient sums forms.
 constexpr int kP64FinChunks = 64;
 
@@ -447,7 +467,7 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
                    int64_t total_src, const Variant &v, bool fwd_sums = true, int terms = 0,
                    bool lean = false) {
   WsLayout L;
-  L.p64 = !lean && p64_active(plan, v, prec, nset, total_src);
+  L.p64 = !lean && p64_active(plan, v, prec, nset, total_src, mode);
   const P64Geometry pg = L.p64 ? p64_geometry(plan, mode, total_src) : P64Geometry{};
   const bool base = !L.p64;  // regions of the per-baseline kernel
   const size_t r4 = prec == RIME_FP64 ? 32 : 16;
@@ -493,8 +513,9 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
                                     (4 * 8 * kWave * 2 * sizeof(uint4) + sizeof(float))
                               : 0;
     const size_t per_t = plane_t * (k3 ? 3 : 2) + frag_t;
-    L.pme_tchunk = static_cast<int32_t>(
-        std::max<size_t>(1, std::min<size_t>(plan->ntime, kPmePlaneBytes / per_t)));
+    // (a pass's timesteps are grid rows, with one more for the scales)
+    L.pme_tchunk = static_cast<int32_t>(std::max<size_t>(
+        1, std::min<size_t>(std::min<int64_t>(plan->ntime, 65534), kPmePlaneBytes / per_t)));
     L.has_k3 = k3;
     L.ph_hi = off;
     off += align_up(plane_t * (k3 ? 3 : 2) * L.pme_tchunk) + 4 * kAlign;
@@ -542,8 +563,7 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
       L.p64_rho = off;
       off += align_up(pg.rho_t * pg.tpass * sizeof(double2));
       L.p64_part = off;
-      off += align_up(static_cast<size_t>(pg.nsg_max) * plan->ntime * pg.ncg * plan->nsub * pg.split * 10 *
-                      kWave * sizeof(double));
+      off += align_up(p64_part_bytes(plan, pg, mode));
       L.pfin = off;
       off += align_up(static_cast<size_t>(pg.nsg_max) * kP64FinChunks * 10 * kWave *
                       sizeof(double2));
@@ -768,7 +788,7 @@ void carve_planes(const rime_plan *plan, const Call &c, const Variant &v, const 
   const int64_t staged = static_cast<int64_t>(plan->tiles[nbt_slot(v.threads)].ntile) *
                          nat_for_host(v.threads) * plan->ntime * plan->nchan * next;
   if (staged >= (int64_t(1) << 24) && c.mode != RIME_MODE_CHI2_GRAD &&
-      L.pme_tchunk >= plan->ntime && v.nc == 2 && v.threads == 256) {
+      L.pme_tchunk >= plan->ntime && plan->nchan <= (1 << 17) && v.nc == 2 && v.threads == 256) {
     p.pl_s0 = c.one.npsrc;
     p.pl_ns = next;
     p.pl_a = reinterpret_cast<float2 *>(take(2 * per_src * next));
@@ -1812,7 +1832,8 @@ static bool batch_engine(const rime_batch *b, int mode, int prec, const Variant 
   const rime_plan *plan = b->plan;
   const int64_t n = b->total_src / b->nset;
   return b->nset > 1 && (prec == RIME_FP64 || (prec == kRes64 && mode == RIME_MODE_CHI2)) &&
-         p64_active(plan, v, RIME_FP64, 1, n) &&
+         p64_active(plan, v, RIME_FP64, 1, n, mode) &&
+         p64_active(plan, v, RIME_FP64, 1, b->max_nsrc, mode) &&
          static_cast<double>(plan->ntime) * plan->nbl * plan->nchan * static_cast<double>(n) >=
              double(1 << 25);
 }

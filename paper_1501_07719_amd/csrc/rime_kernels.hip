@@ -83,8 +83,9 @@ __global__ __launch_bounds__(256) void prep_sources(const KParams p, int nc) {
     const int64_t row = p.p64_ns ? 0 : g * p.nchan, step = p.p64_ns ? p.p64_ns : 1;
     R4 *st = static_cast<R4 *>(p.src_st) + row + (p.p64_ns ? s : 0);
     R *sf = static_cast<R *>(p.src_sf) + row + (p.p64_ns ? s : 0);
-    const int c1 = min(p.nchan, static_cast<int>(blockIdx.z + 1) * kPrepCh);
-    for (int c = blockIdx.z * kPrepCh; c < c1; ++c) {
+    const int per = (p.nchan + gridDim.z - 1) / gridDim.z;
+    const int c1 = min(p.nchan, static_cast<int>(blockIdx.z + 1) * per);
+    for (int c = blockIdx.z * per; c < c1; ++c) {
       const double f = exp(a * p.lnfr[c]);
       R4 v;
       v.x = static_cast<R>(f * I);
@@ -1392,7 +1393,8 @@ hipError_t launch_prep(const KParams &p, bool fp64, int max_nsrc, int rec_nc,
   // per timestep after the per-set rows); one workgroup per set row at least,
   // which writes the set's domain flag also for a sky without sources
   const int nblk = max_nsrc > 0 ? (max_nsrc + 255) / 256 : 1;
-  const dim3 grid(nblk, p.nset + (rec_nc > 0 ? p.ntime : 0), (p.nchan + kPrepCh - 1) / kPrepCh);
+  const dim3 grid(nblk, p.nset + (rec_nc > 0 ? p.ntime : 0),
+                  min((p.nchan + kPrepCh - 1) / kPrepCh, 1 << 15));
   if (fp64)
     hipLaunchKernelGGL(prep_sources<double>, grid, dim3(256), 0, stream, p, rec_nc);
   else
