@@ -86,7 +86,7 @@ template <> struct Num<double> {
   // two operations; the quadrant permutes and negates the pair.  About 30
   // instructions against 70 of sincospi() (8 antennas, 31 timesteps, 60
   // channels, 24 points, no beam, predict: 24.3 against 41.9 us with the beam's
-  // own polynomials below; 64-antenna planes 3.0 -> 2.4 ms).
+  // own polynomials below; 64-antenna planes with k3 4.0 -> 3.4 ms).
   __device__ static inline void sincos_turns(double r, double *s, double *c) {
     const double q = rint(4.0 * r);
     const double x = fma(-0.25, q, r);

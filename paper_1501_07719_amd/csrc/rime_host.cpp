@@ -763,15 +763,21 @@ struct Call {
 // extended sources that rime_main stages from.  Both take the same bytes per
 // source, so the region, sized for the call's sources, holds any split.
 // Extended sources get planes in the forward-only modes of the 256-thread
-// kernels when one pass over time holds them all: there every antenna's terms
-// would be formed by (tiles per antenna) workgroups (64 antennas, 500
-// Gaussians, 6400 (timestep, channel): 4 times; the kernel takes 4.26 ms with
-// planes, which take 0.52 ms, and 5.79 ms without).  The planes cost a launch
-// of about 6 us, which these kernels save from about 2^24 terms formed in
+// kernels and in the gradient mode when one pass over time holds them all:
+// there every antenna's terms would be formed by (tiles per antenna)
+// workgroups, in the gradient twice (64 antennas, 500 Gaussians, 6400
+// (timestep, channel): the forward's kernel takes 4.26 ms with planes, which
+// take 0.52 ms, and 5.79 ms without; the gradient's 14.0 ms with planes, which
+// take 0.66 ms with k3, and 15.3 ms without).  The planes cost a launch of
+// about 6 us, which the forward saves from about 2^24 terms formed in
 // workgroups on (84 antennas, 29 Gaussians, 10 (timestep, channel): 38.4
-// against 36.4 us without planes).  In the gradient modes (1024 threads, half
-// the tiles per antenna, most of the time in the adjoint) they do not pay: 12
-// proposals over 64 antennas, 50 timesteps, 32 channels 42.5 against 42.0 ms.
+// against 36.4 us without planes), and the gradient well before 2^21 (84
+// antennas, 200 (timestep, channel), 3e6 terms: 294 against 297 us; 30
+// antennas, 640 (timestep, channel), 1.0e7 terms: 407 against 446 us).
+// Without planes run: gradients with per-call terms, whose kernel then spills
+// more (50 antennas, 777 (timestep, channel): 1.58 against 1.53 ms with all
+// kernels), and the adjoint of the float64-residual mode, which stages once
+// (36.0 ms for the call either way).
 void carve_planes(const rime_plan *plan, const Call &c, const Variant &v, const WsLayout &L,
                   char *w, KParams &p) {
   const size_t per_src = static_cast<size_t>(plan->nchan) * plan->nap * L.pme_tchunk * 4;
@@ -787,11 +793,15 @@ void carve_planes(const rime_plan *plan, const Call &c, const Variant &v, const 
   const int next = c.max_nsrc - c.one.npsrc;
   const int64_t staged = static_cast<int64_t>(plan->tiles[nbt_slot(v.threads)].ntile) *
                          nat_for_host(v.threads) * plan->ntime * plan->nchan * next;
-  if (staged >= (int64_t(1) << 24) && c.mode != RIME_MODE_CHI2_GRAD &&
-      L.pme_tchunk >= plan->ntime && plan->nchan <= (1 << 17) && v.nc == 2 && v.threads == 256) {
+  const bool grad = c.mode == RIME_MODE_CHI2_GRAD;
+  const bool k3 = grad && plan->beam;
+  if (staged >= (int64_t(1) << (grad ? 21 : 24)) && L.pme_tchunk >= plan->ntime && plan->nchan <= (1 << 17) &&
+      v.nc == 2 &&
+      (grad ? L.pme_adj && c.prec == RIME_MIXED && !c.die && !c.stokes_t : v.threads == 256)) {
     p.pl_s0 = c.one.npsrc;
     p.pl_ns = next;
     p.pl_a = reinterpret_cast<float2 *>(take(2 * per_src * next));
+    if (k3) p.pl_k3 = reinterpret_cast<float *>(take(per_src * next));
     p.pme_t0 = 0;
     p.pme_nt = plan->ntime;
   }
@@ -892,6 +902,7 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
   if (L.pme_tchunk > 0) {
     p.nap = plan->nap;
     carve_planes(plan, c, v, L, w, p);
+    if (L.pme_adj) p.src_f = reinterpret_cast<float *>(w + L.src_f);
   }
   if (L.pme_tchunk > 0 && c.one.npsrc > 0) {
     p.pme = 1;
@@ -916,7 +927,6 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
       p.pfin = reinterpret_cast<double2 *>(w + L.pfin);
       p.pme_fchunk = pme_fin_nchunk(
           p.pme_nsr, static_cast<int64_t>(plan->ntime) * p.pme_ncg * plan->nblk * p.pme_nqr);
-      p.src_f = reinterpret_cast<float *>(w + L.src_f);
       p.mfrag = reinterpret_cast<uint4 *>(w + L.mfrag);
       p.mscale = reinterpret_cast<float *>(w + L.mscale);
     }

@@ -152,8 +152,10 @@ struct KParams {
   uint4 *mfrag;            // [pme_nt][nchan][nblk][nqr][4][8][64][2] fp16 fragments of M
   float *mscale;           // [pme_nt][nchan][nblk][nqr] 2^e undoing the fragment scale
   // float32 planes of the extended sources (pl_ns from pl_s0 on), a_ps = e_ps K_ps
-  // [pme_nt][nchan][pl_ns][nap], or nullptr: rime_main stages from them
+  // [pme_nt][nchan][pl_ns][nap], or nullptr: rime_main stages from them; in
+  // gradient mode with a beam also k3 (d ln e / d(l, m) = k3 (l - dl_p, m - dm_p))
   float2 *pl_a;
+  float *pl_k3;
   int32_t pl_s0, pl_ns;
   // float64 engine (rime_p64.hip): planes of every source [pme_nt][nchan]
   // [nap][p64_ns] (k3 in gradient calls with a beam), the baselines' vectors

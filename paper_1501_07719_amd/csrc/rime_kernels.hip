@@ -243,14 +243,19 @@ __device__ inline void stage_tile(const KParams &p, const SetDesc &sd, int t, in
   const int tid = threadIdx.x;
   if constexpr (PL) {
     // the terms come from the planes; all loads of a thread are issued before
-    // the first one is used
-    static_assert(!WITH_BETA && NS * NAT % NBT == 0, "whole rounds, forward only");
+    // the first one is used.  Loading the next tile's lines into L2 ahead cost
+    // more than it hid (its registers spill in the loops: 14.5 against 14.0 ms
+    // for 64 antennas, 500 Gaussians, 6400 (timestep, channel)).
+    static_assert(NS * NAT % NBT == 0, "whole rounds");
     const int64_t plane = static_cast<int64_t>(p.pl_ns) * p.nap;
-    const float2 *pa = p.pl_a +
-                       (static_cast<int64_t>(t - p.pme_t0) * p.nchan + c0) * plane +
-                       static_cast<int64_t>(s0 - p.pl_s0) * p.nap;
+    const int64_t base = (static_cast<int64_t>(t - p.pme_t0) * p.nchan + c0) * plane +
+                         static_cast<int64_t>(s0 - p.pl_s0) * p.nap;
+    const float2 *pa = p.pl_a + base;
+    const float *pk = p.pl_k3 + base;
+    const bool beta = WITH_BETA && p.beam;  // (the adjoint reads beta with a beam only)
     constexpr int NI = NS * NAT / NBT;
     R2 va[NI][NC];
+    R vk[NI][NC];
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int idx = tid + i * NBT;
@@ -260,8 +265,11 @@ __device__ inline void stage_tile(const KParams &p, const SetDesc &sd, int t, in
       const int64_t o = static_cast<int64_t>(s) * p.nap + ant;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
-        va[i][c].x = va[i][c].y = R(0);
-        if (ok && c < ncv) va[i][c] = pa[c * plane + o];
+        va[i][c].x = va[i][c].y = vk[i][c] = R(0);
+        if (ok && c < ncv) {
+          va[i][c] = pa[c * plane + o];
+          if (beta) vk[i][c] = pk[c * plane + o];
+        }
       }
     }
 #pragma unroll
@@ -270,6 +278,18 @@ __device__ inline void stage_tile(const KParams &p, const SetDesc &sd, int t, in
       const int s = idx / NAT, ai = idx - s * NAT;
 #pragma unroll
       for (int c = 0; c < NC; ++c) s_a[s * L::AST + ai * NC + c] = va[i][c];
+      if (beta) {
+        // (a source past the tile's end has k3 = 0)
+        const double4 g = p.src_geo[sd.src_off + s0 + min(s, cnt - 1)];
+        const R dl = static_cast<R>(g.x - s_pnt[ai][0]), dm = static_cast<R>(g.y - s_pnt[ai][1]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          R2 b;
+          b.x = vk[i][c] * dl;
+          b.y = vk[i][c] * dm;
+          s_beta[s * L::AST + ai * NC + c] = b;
+        }
+      }
     }
   } else {
     for (int idx = tid; idx < NS * NAT; idx += NBT) {
@@ -607,12 +627,12 @@ __device__ inline void adjoint_pair(int wave, int nw, int nact, int hb, const fl
     }
   };
   const int npair = nact >> 1;
-  // records are read one pair ahead (the record array is padded)
-  float4 geo_n = rec[2 * wave + hb];
+  // (the records by a 32-bit offset from the tile's uniform base)
+  const char *rb = reinterpret_cast<const char *>(rec);
+  uint32_t ro = static_cast<uint32_t>(2 * wave + hb) * sizeof(float4);
   for (int bj = wave; bj < npair; bj += nw) {
-    const float4 geo = geo_n;
-    geo_n = rec[2 * (bj + nw) + hb];
-    body(geo, 2 * bj + hb);
+    body(*reinterpret_cast<const float4 *>(rb + ro), 2 * bj + hb);
+    ro += 2 * nw * sizeof(float4);
   }
   if ((nact & 1) && hb == 0 && wave == npair % nw) body(rec[nact - 1], nact - 1);
 }
@@ -653,7 +673,16 @@ void rime_main(const KParams p) {
   double2 *s_scr = reinterpret_cast<double2 *>(smem + L::OFF_SCR);
 
   // ---- work item ----------------------------------------------------------
-  const int item = blockIdx.x;
+  // With planes, the tiles of one (time chunk, channel block) go to one XCD
+  // (workgroup i runs on XCD i % 8), whose L2 then reads each plane once for
+  // all of them: windows of 8 channel blocks, item = (XCD, tile).  197
+  // antennas, 19 tiles: gradient call 204.0 -> 200.2 ms.
+  int item = blockIdx.x;
+  if constexpr (PL) {
+    const int span = 8 * p.ntile, w0 = item / span * span;
+    if (w0 + span <= static_cast<int>(gridDim.x))
+      item = w0 + (item - w0) % 8 * p.ntile + (item - w0) / 8;
+  }
   const int set_rank = item / p.items_per_set;
   const int local_item = item - set_rank * p.items_per_set;
   const int set = p.order ? const_ptr<int32_t>(p.order)[set_rank] : set_rank;
@@ -905,8 +934,8 @@ void rime_main(const KParams p) {
         const bool shaped = tl.shape != SHAPE_POINT;
         const bool disk = tl.shape == SHAPE_DISK;
         __syncthreads();
-        stage_tile<R, NBT, NC, NS, MODE, true, TERMS, false>(p, sd, t, tile, s0, cnt, shaped, c0, ncv,
-                                                      s_uvw, s_pnt, s_a, s_beta, s_src);
+        stage_tile<R, NBT, NC, NS, MODE, true, TERMS, PL>(p, sd, t, tile, s0, cnt, shaped, c0, ncv,
+                                                          s_uvw, s_pnt, s_a, s_beta, s_src);
         __syncthreads();
         R gl[10];
 #pragma unroll
@@ -957,9 +986,17 @@ void rime_main(const KParams p) {
                                                      st1, e, pk, a);
             }
             // assemble this half's sums over its baselines (both channels)
-            const double al = sd.alpha[s0 + sl];
-            const float f0 = static_cast<float>(exp(al * lnfr2[0]));
-            const float f1 = static_cast<float>(exp(al * lnfr2[1]));
+            float f0, f1;
+            if constexpr (PL) {
+              // (nu/nu_ref)^alpha as the preparation formed it
+              const int64_t fi = (sd.src_off + s0 + sl) * p.nchan + c0;
+              f0 = p.src_f[fi];
+              f1 = p.src_f[fi + (ncv > 1)];
+            } else {
+              const double al = sd.alpha[s0 + sl];
+              f0 = static_cast<float>(exp(al * lnfr2[0]));
+              f1 = static_cast<float>(exp(al * lnfr2[1]));
+            }
             const float lon = static_cast<float>(lo.x), mon = static_cast<float>(lo.y);
             gl[0] = a.g5[0] + a.g5[1] + (a.G[0] - lon * a.G[2]);
             gl[1] = a.g6[0] + a.g6[1] + (a.G[1] - mon * a.G[2]);
@@ -1363,20 +1400,24 @@ hipError_t launch_sum_chunks(const double *part, int nchunk, int64_t stride, int
 
 // The instantiation with per-call terms runs only when a call has them, and
 // the one that stages from planes (PL) when the call's extended sources have
-// planes (the forward modes of the float32 256-thread kernel).
+// planes (float32, two channels per thread: the forward modes of the 256-thread
+// kernel and the gradient without per-call terms).
 template <class R, int NBT, int NC, int NS, int MODE>
 static hipError_t launch_main(const KParams &p, int nitems, hipStream_t stream) {
   const dim3 grid(nitems), block(NBT);
   const bool terms = p.die || p.stokes_t;
-  if constexpr (sizeof(R) == 4 && NBT == 256 && NC == 2 &&
-                (MODE == MODE_PREDICT || MODE == MODE_CHI2)) {
+  if constexpr (sizeof(R) == 4 && NBT >= 256 && NC == 2 &&
+                (MODE == MODE_GRAD || (NBT == 256 && MODE != MODE_ADJ))) {
     if (p.pl_a) {
-      if (terms)
-        hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, true, true>), grid, block, 0, stream,
-                           p);
-      else
-        hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, false, true>), grid, block, 0, stream,
-                           p);
+      if constexpr (MODE != MODE_GRAD) {
+        if (terms) {
+          hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, true, true>), grid, block, 0,
+                             stream, p);
+          return hipGetLastError();
+        }
+      }
+      hipLaunchKernelGGL((rime_main<R, NBT, NC, NS, MODE, false, true>), grid, block, 0, stream,
+                         p);
       return hipGetLastError();
     }
   }

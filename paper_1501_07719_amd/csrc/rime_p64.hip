@@ -20,10 +20,10 @@
 //
 // Bound by float64 instruction issue (the chip holds about 1.9 GHz under them).
 // 64 antennas, 100 timesteps, 64 channels, 1000 points + 500 Gaussians, beam:
-//   planes 4.0 ms (with k3), forward 17.4 ms (12 instructions per point term
+//   planes 2.9 ms (3.4 ms with k3), forward 17.4 ms (12 instructions per point term
 //   and 37 per Gaussian term, 76 % of issue slots used), adjoint 18.2 ms for
 //   the points (28 per term, 77 %) and 17.0 ms for the Gaussians (61, 80 %);
-//   chi^2 + gradient 57.3 ms, chi^2 20.2 ms, against 88.5 and 27.3 ms on the
+//   chi^2 + gradient 56.1 ms, chi^2 19.6 ms, against 88.5 and 27.3 ms on the
 //   per-baseline kernel.
 // Measured and not kept: point-source sums on v_mfma_f64_16x16x4_f64 (forward
 // 9.4 ms for the points alone; float64 matrix and vector instructions have the

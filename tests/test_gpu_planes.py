@@ -43,3 +43,34 @@ def test_planes_equal_in_kernel_staging(na, ntime, nchan, ng, nx):
     assert torch.equal(vis[0], vis[1])
     assert chi[0] == chi[1]
     plan.close()
+
+
+# the gradient of the 256- and the 1024-thread kernel, whose adjoint also stages
+# the beam-gradient factor
+@pytest.mark.parametrize("off,on", [(2, 4), (1, 5)])
+@pytest.mark.parametrize("na,ntime,nchan,ng,nx,beam", [
+    (17, 2, 5, 31, 33, True), (17, 60, 151, 31, 33, True), (64, 21, 99, 33, 1, True),
+    (50, 37, 51, 0, 65, False)])
+def test_gradient_planes_equal_in_kernel_staging(off, on, na, ntime, nchan, ng, nx, beam):
+    pr = make_problem("c1", ntime=ntime, nchan=nchan, npsrc=0, ngsrc=ng, na=na, key=92)
+    if not beam:
+        pr.obs.beam = False
+    prec = R.MIXED
+    sky = R.DeviceSky.from_host(add_disks(pr.sky, nx, rngs(92)[5]))
+    D = torch.as_tensor(pr.noise.astype(np.complex64), device="cuda")
+    W = torch.as_tensor(pr.weight.astype(np.float32), device="cuda")
+    plan = R.Plan(pr.obs)
+    out = []
+    for vi in (off, on):
+        assert R.rime_variant_info(R.MODE_CHI2_GRAD, prec, vi)[0] == (256 if vi in (1, 5) else 1024)
+        plan.set_variant(R.MODE_CHI2_GRAD, prec, vi)
+        ws = R.workspace(plan, R.MODE_CHI2_GRAD, prec, 1, sky.nsrc)
+        c = torch.empty(1, dtype=torch.float64, device="cuda")
+        g = torch.full((sky.nsrc, 10), float("nan"), dtype=torch.float64, device="cuda")
+        R.rime_chi2_grad(plan, sky, prec, D, W, c, g, ws)
+        out.append((c.item(), g))
+    torch.cuda.synchronize()
+    assert torch.isfinite(out[0][1]).all()
+    assert out[0][0] == out[1][0]
+    assert torch.equal(out[0][1], out[1][1])
+    plan.close()
