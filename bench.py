@@ -854,7 +854,8 @@ def write_traffic(pairs, out_path, workload="c2"):
     import re
     import statistics
 
-    pat = re.compile(r"rime_main<float, (\d+), (\d+), (\d+), 2, false>")
+    # (the last argument, when there is one: staged from planes or not)
+    pat = re.compile(r"rime_main<float, (\d+), (\d+), (\d+), 2, false(?:, (?:true|false))?>")
 
     def read(path):
         rows = list(csv.DictReader(open(path)))

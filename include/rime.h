@@ -149,7 +149,9 @@ void rime_plan_destroy(rime_plan *plan);
 /* Bytes of device workspace that one call of `mode` needs for `nset` sets with
  * `total_src` sources in all (nset = 1 for the single-sky calls, where
  * total_src may be 0; otherwise total_src >= nset).  0 for invalid
- * arguments. */
+ * arguments.  With a float64 forward on large arrays it includes the
+ * per-antenna planes of the float64 engine; a call with less, but enough for
+ * the per-baseline kernel, is accepted and runs on that kernel. */
 size_t rime_workspace_size(const rime_plan *plan, rime_mode mode, rime_precision prec,
                            int32_t nset, int64_t total_src);
 
@@ -217,8 +219,8 @@ rime_status rime_chi2_ex(const rime_plan *plan, const rime_sky *sky, const rime_
  * rime_chi2_grad without a workspace argument.  The workspace is a fixed
  * 32 MiB block of device memory inside the library, one per device, held
  * until the process ends; the call allocates nothing.  A call whose
- * workspace need (rime_workspace_size for mode RIME_MODE_CHI2_GRAD, one set,
- * the sky's sources, with the plan's variant) exceeds 32 MiB returns
+ * workspace need (the least that a RIME_MODE_CHI2_GRAD call of one set, the
+ * sky's sources and the plan's variant accepts) exceeds 32 MiB returns
  * RIME_ERR_WORKSPACE and enqueues nothing.  Every call on one device shares
  * the block: calls that overlap on one device (on different streams, or
  * from different host threads) race and must be serialised by the caller.
@@ -336,7 +338,9 @@ rime_status rime_variant_info(rime_mode mode, rime_precision prec, int32_t index
  * A batched call with such a variant runs the single-sky pipeline once per
  * set, alternating between two streams (workspace: one set's per stream, as
  * rime_batch_workspace_size counts it; rime_workspace_size with the batch's
- * nset and total source count is never smaller).  For RIME_MIXED_RES64 the
+ * nset and total source count is never smaller).  Large float64 sets also run
+ * one by one when the workspace is of rime_batch_workspace_size; with
+ * rime_workspace_size bytes all sets share one launch sequence.  For RIME_MIXED_RES64 the
  * chi-squared variants are the float64 forwards and the gradient variants
  * the float32 adjoints (the forward of a gradient call is the plan's
  * RIME_MODE_CHI2 variant of that precision). */

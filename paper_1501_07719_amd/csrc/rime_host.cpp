@@ -1200,8 +1200,8 @@ int default_variant(const rime_plan *plan, int mode, int prec) {
   // float32-mixed 4 / 5 -> 1024 / 256 threads with the point sources on the
   // matrix cores (measured faster from 64 antennas up); the 1024-thread one
   // for the gradient from 1024 baselines up (2016 baselines: whole call
-  // 22.7 ms against 23.0 ms; 19306 baselines: per-baseline kernel 123.7 ms
-  // against 150.6 ms); small arrays take 1 in both
+  // 21.2 ms against 22.5 ms; 19306 baselines: per-baseline kernel 114.0 ms
+  // against 131.1 ms); small arrays take 1 in both
   // precisions (7 antennas, 10 timesteps, 16 channels, 20 sources, one graph
   // launch of chi2 + gradient: FP64 30 us against 34 us for 0, float32-mixed
   // 26 us against 28 us for 0 and 75 us for 5).  The float64-residual mode
