@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256) void p64_planes(const KParams p) {
   const int ce = min(p.nchan, cb + p.phase_nc);
   const int a = static_cast<int>(idx / p.p64_ns);
   const int s = static_cast<int>(idx - static_cast<int64_t>(a) * p.p64_ns);
-  if (s >= p.total_src) return;  // row padding, never read
+  if (s >= p.total_src) return;  // row padding, never used
   const int64_t o = static_cast<int64_t>(tt) * p.nchan * plane + idx;
   double2 *pa = p.p64_a + o;
   double *pk = p.p64_k3 + o;
@@ -425,9 +425,10 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
     const int64_t ro = pc * plane + s;
     const double2 *col = p.p64_a + ro;  // this source's terms, p.p64_ns apart
     // without a beam the loads of k3 stay (a wait must not depend on a
-    // branch), from the other plane, and count as zero
-    const double *k3 = (p.p64_k3 ? p.p64_k3 : reinterpret_cast<const double *>(p.p64_a)) + ro;
-    const double k3_on = p.p64_k3 ? 1.0 : 0.0;
+    // branch), from the other plane, and what they read (padding that no
+    // kernel writes among it) is replaced by zero, not multiplied by it
+    const bool beam = p.p64_k3 != nullptr;
+    const double *k3 = (beam ? p.p64_k3 : reinterpret_cast<const double *>(p.p64_a)) + ro;
     const double2 *rho = p.p64_rho + (pc * p.npair * (kPmeBlk * kPmeBlk) + slot0) * 4 + lrho;
     const int64_t cs = static_cast<int64_t>(c) * p.p64_ns + s;
     const double f = static_cast<const double *>(p.src_sf)[cs];
@@ -448,7 +449,7 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
       o1 += uv.x * sI;
       o2 += uv.y * sI;
       o3 += w.x * sI;
-      const double kR = k3_on * k * sR;
+      const double kR = beam ? k * sR : 0.0;
       bl += kR * (sg.x - pl.x);
       bm += kR * (sg.y - pl.y);
     };

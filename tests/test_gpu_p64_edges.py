@@ -1,0 +1,51 @@
+"""Edge cases of the float64 engine's routes, against the per-baseline kernel
+(variant 0, which never takes the engine) to the float64 bar, or bitwise against
+the resident single-sky call where both run on the engine."""
+import numpy as np
+import pytest
+
+from rime_synth import Observation
+from tests._helpers import TOL, grad_errors, rel
+from tests.test_gpu_p64 import problem
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+R = pytest.importorskip("paper_1501_07719_amd")
+F64 = dict(dtype=torch.float64, device="cuda")
+
+
+def dev(D, W, prec=0):
+    if prec != R.FP64:
+        D, W = D.astype(np.complex64), W.astype(np.float32)
+    return torch.as_tensor(D, device="cuda"), torch.as_tensor(W, device="cuda")
+
+
+def gradient(obs, sky, D, W, variant=1, fill=0xFF, prec=0, ws_bytes=None):
+    """chi^2 and gradient of one sky, over a workspace of `fill` bytes."""
+    plan = R.Plan(obs)
+    if prec == R.FP64:
+        plan.set_variant(R.MODE_CHI2_GRAD, prec, variant)
+    Dd, Wd = dev(D, W, prec)
+    n = ws_bytes or plan.workspace_size(R.MODE_CHI2_GRAD, prec, 1, sky.nsrc)
+    ws = torch.full((n,), fill, dtype=torch.uint8, device="cuda")
+    chi2, grad = torch.empty(1, **F64), torch.full((sky.nsrc, 10), float("nan"), **F64)
+    R.rime_chi2_grad(plan, R.DeviceSky.from_host(sky), prec, Dd, Wd, chi2, grad, ws)
+    torch.cuda.synchronize()
+    plan.close()
+    return chi2.item(), grad.cpu().numpy()
+
+
+def check(a, b, sky):
+    assert np.isfinite(a[1]).all()
+    assert rel(a[0], b[0]) <= TOL[0]
+    errs = grad_errors(a[1], b[1], sky.npsrc)
+    assert max(errs.values()) <= TOL[0], errs
+
+
+@pytest.mark.parametrize("npsrc,ng,nx", [(33, 0, 0), (0, 49, 0), (65, 0, 35), (32, 33, 0)])
+def test_gradient_without_beam_ignores_the_workspace(npsrc, ng, nx):
+    """Source counts that leave padding in the planes' rows (33, 49, 100, 65 of
+    40, 56, 104, 72): what the workspace held before must not reach the sums."""
+    obs, sky, D, W = problem(17, 2, 3, npsrc, ng, nx, "", beam=False)
+    check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
