@@ -55,7 +55,9 @@ __global__ __launch_bounds__(256) void p64_planes(const KParams p) {
   const int64_t o = static_cast<int64_t>(tt) * p.nchan * plane + idx;
   double2 *pa = p.p64_a + o;
   double *pk = p.p64_k3 + o;
-  if (a >= p.na) {
+  // antennas past the array, and those without baselines, whose coordinates
+  // may be undefined: the adjoint weights their terms with sums of zero
+  if (a >= p.na || p.ant_off[a] == p.ant_off[a + 1]) {
     for (int c = cb; c < ce; ++c) {
       pa[c * plane] = make_double2(0.0, 0.0);
       if (WITH_K3) pk[c * plane] = 0.0;
@@ -388,15 +390,18 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
   const int2 blk = p.pair_blk[pair];
   const int P0 = __builtin_amdgcn_readfirstlane(blk.x) * kPmeBlk + si * 16;
   const int Q0 = __builtin_amdgcn_readfirstlane(blk.y) * kPmeBlk + sj * 16;
-  // row masks, one per lane; antennas past the array have no baseline
+  // row masks, one per lane; the coordinates of antennas without baselines
+  // (and past the array) count as zero
   const uint32_t maskv = p.pair_mask[pair * kPmeBlk + si * 16 + (lane & 15)];
   if (lane < 32) {
-    const int a = min(lane < 16 ? P0 + lane : Q0 + lane - 16, p.na - 1);
+    const int i = lane < 16 ? P0 + lane : Q0 + lane - 16, a = min(i, p.na - 1);
+    const bool held = i == a && p.ant_off[a] != p.ant_off[a + 1];
     const double *x = p.uvw + (static_cast<int64_t>(t) * p.na + a) * 3;
     const double *q = p.pointing + (static_cast<int64_t>(t) * p.na + a) * 2;
-    lds.ant[lane][0] = make_double2(x[0], x[1]);
-    lds.ant[lane][1] = make_double2(x[2], 0.0);
-    lds.ant[lane][2] = make_double2(q[0], q[1]);
+    const double2 zero = make_double2(0.0, 0.0);
+    lds.ant[lane][0] = held ? make_double2(x[0], x[1]) : zero;
+    lds.ant[lane][1] = held ? make_double2(x[2], 0.0) : zero;
+    lds.ant[lane][2] = held ? make_double2(q[0], q[1]) : zero;
   }
   const int64_t plane = static_cast<int64_t>(p.nap) * p.p64_ns;
   const int64_t slot0 = static_cast<int64_t>(pair) * (kPmeBlk * kPmeBlk) + si * 16 * kPmeBlk +

@@ -49,3 +49,21 @@ def test_gradient_without_beam_ignores_the_workspace(npsrc, ng, nx):
     40, 56, 104, 72): what the workspace held before must not reach the sums."""
     obs, sky, D, W = problem(17, 2, 3, npsrc, ng, nx, "", beam=False)
     check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
+
+
+@pytest.mark.parametrize("beam", [True, False])
+@pytest.mark.parametrize("dead", [[5], [3, 16], [0, 17, 32]])
+def test_antennas_without_baselines(dead, beam):
+    """An antenna that no baseline holds may have undefined coordinates and
+    pointing: the gradient must not depend on them."""
+    obs, sky, D, W = problem(33, 2, 3, 40, 36, 0, "", beam=beam)
+    keep = ~(np.isin(obs.ant1, dead) | np.isin(obs.ant2, dead))
+    uvw = obs.uvw.copy()
+    uvw[:, dead] = np.nan
+    pnt = None if obs.pointing is None else obs.pointing.copy()
+    if pnt is not None:
+        pnt[:, dead] = np.nan
+    obs = Observation(**{**obs.__dict__, "ant1": obs.ant1[keep], "ant2": obs.ant2[keep],
+                         "uvw": uvw, "pointing": pnt})
+    D, W = np.ascontiguousarray(D[:, keep]), np.ascontiguousarray(W[:, keep])
+    check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
