@@ -365,7 +365,8 @@ __global__ __launch_bounds__(256, 2) void p64_forward(const KParams p) {
 // (P = c sum_k St'_k rho_k) stay in registers, the rows pass by, and the
 // residual and baseline vector of a slot are scalar.  With the row and column
 // sums of P the position gradient needs no per-baseline factor:
-//   sum (u_p - u_q) Im P        = sum_p u_p row_p - sum_q u_q col_q,
+//   sum (u_p - u_q) Im P        = sum_p u_p row_p - sum_q u_q col_q
+//                                 (u from an origin inside the sub-block),
 //   sum (beta_p + beta_q) Re P  = sum_p beta_p row_p + sum_q beta_q col_q.
 // The Stokes and shape sums are those of adjoint_loop (rime_kernels.hip).
 // ---------------------------------------------------------------------------
@@ -391,16 +392,22 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
   const int P0 = __builtin_amdgcn_readfirstlane(blk.x) * kPmeBlk + si * 16;
   const int Q0 = __builtin_amdgcn_readfirstlane(blk.y) * kPmeBlk + sj * 16;
   // row masks, one per lane; the coordinates of antennas without baselines
-  // (and past the array) count as zero
+  // (and past the array) count as zero.  The coordinates are taken from the
+  // first row's antenna that holds a baseline here: only differences enter,
+  // and an offset common to all antennas would otherwise cost digits in the
+  // difference of the row and column sums
   const uint32_t maskv = p.pair_mask[pair * kPmeBlk + si * 16 + (lane & 15)];
+  const uint64_t rows = __ballot(((maskv >> (sj * 16)) & 0xffffu) != 0u);
+  const double *x0 = p.uvw + (static_cast<int64_t>(t) * p.na + P0 +
+                              __builtin_amdgcn_readfirstlane(__builtin_ctzll(rows))) * 3;
   if (lane < 32) {
     const int i = lane < 16 ? P0 + lane : Q0 + lane - 16, a = min(i, p.na - 1);
     const bool held = i == a && p.ant_off[a] != p.ant_off[a + 1];
     const double *x = p.uvw + (static_cast<int64_t>(t) * p.na + a) * 3;
     const double *q = p.pointing + (static_cast<int64_t>(t) * p.na + a) * 2;
     const double2 zero = make_double2(0.0, 0.0);
-    lds.ant[lane][0] = held ? make_double2(x[0], x[1]) : zero;
-    lds.ant[lane][1] = held ? make_double2(x[2], 0.0) : zero;
+    lds.ant[lane][0] = held ? make_double2(x[0] - x0[0], x[1] - x0[1]) : zero;
+    lds.ant[lane][1] = held ? make_double2(x[2] - x0[2], 0.0) : zero;
     lds.ant[lane][2] = held ? make_double2(q[0], q[1]) : zero;
   }
   const int64_t plane = static_cast<int64_t>(p.nap) * p.p64_ns;

@@ -67,3 +67,15 @@ def test_antennas_without_baselines(dead, beam):
                          "uvw": uvw, "pointing": pnt})
     D, W = np.ascontiguousarray(D[:, keep]), np.ascontiguousarray(W[:, keep])
     check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
+
+
+@pytest.mark.parametrize("ng", [0, 40])
+def test_common_offset_of_the_antenna_coordinates(ng):
+    """Only coordinate differences enter the model; antennas given from the
+    Earth's centre (6.4e6 m) instead of the array's keep the gradient's
+    accuracy.  The baselines are as in the centred array to 6.4e6 2^-53 =
+    7e-10 m, and both kernels see the same ones."""
+    obs, sky, D, W = problem(20, 2, 4, 64, ng, 0, "")
+    uvw = obs.uvw * 0.05 + np.array([6.4e6, -3.1e6, 2.2e6])
+    obs = Observation(**{**obs.__dict__, "uvw": uvw})
+    check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
