@@ -1910,8 +1910,12 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
     if (!per_set) {
       Call c = base;
       c.nset = b->nset;
-      c.d_sets = b->d_sets;
-      c.d_order = b->d_order;
+      if (b->nset > 1) {
+        c.d_sets = b->d_sets;
+        c.d_order = b->d_order;
+      } else {
+        c.one = b->h_sets[0];  // a batch of one set is a single-sky call
+      }
       c.max_nsrc = b->max_nsrc;
       c.total_src = b->total_src;
       c.chi2 = chi2;

@@ -79,3 +79,39 @@ def test_common_offset_of_the_antenna_coordinates(ng):
     uvw = obs.uvw * 0.05 + np.array([6.4e6, -3.1e6, 2.2e6])
     obs = Observation(**{**obs.__dict__, "uvw": uvw})
     check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
+
+
+@pytest.mark.parametrize("prec", [0, 2])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_of_one_set(prec, graph):
+    obs, sky, D, W = problem(20, 2, 5, 40, 30, 10, "")
+    plan = R.Plan(obs)
+    Dd, Wd = dev(D, W, prec)
+    ds = R.DeviceSky.from_host(sky)
+    batch = R.Batch(plan, [ds])
+    got, ref = [], []
+    with torch.cuda.stream(torch.cuda.Stream()):
+        for mode in (R.MODE_CHI2, R.MODE_CHI2_GRAD):
+            for vi in range(R.rime_variant_count(mode, prec)):
+                plan.set_variant(mode, prec, vi)
+                chi2, grad = torch.full((1,), -1.0, **F64), torch.full((sky.nsrc, 10), -1.0, **F64)
+                g = grad if mode == R.MODE_CHI2_GRAD else None
+                ws = torch.empty(batch.workspace_size(mode, prec), dtype=torch.uint8,
+                                 device="cuda")
+                for _ in range(2):
+                    R.rime_chi2_batched(batch, prec, Dd, Wd, chi2, g, ws, use_graph=graph)
+                torch.cuda.current_stream().synchronize()
+                got.append((chi2.item(), grad.cpu().numpy()))
+                chi2, grad = torch.full((1,), -1.0, **F64), torch.full((sky.nsrc, 10), -1.0, **F64)
+                ws = R.workspace(plan, mode, prec, 1, sky.nsrc)
+                if mode == R.MODE_CHI2:
+                    R.rime_chi2(plan, ds, prec, Dd, Wd, chi2, ws)
+                else:
+                    R.rime_chi2_grad(plan, ds, prec, Dd, Wd, chi2, grad, ws)
+                torch.cuda.current_stream().synchronize()
+                ref.append((chi2.item(), grad.cpu().numpy()))
+    for a, b in zip(got, ref):
+        assert a[0] == b[0]
+        np.testing.assert_array_equal(a[1], b[1])
+    batch.close()
+    plan.close()
