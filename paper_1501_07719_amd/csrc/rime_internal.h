@@ -110,7 +110,7 @@ struct KParams {
   void *vis;               // predict output
   double2 *chi2_part;      // [nset][chi2_items] (sum, compensation)
   int32_t chi2_items;      // chi^2 partials per set
-  int32_t fin_chi2;        // finalize_grad1: sets whose chi^2 it forms (set at launch)
+  int32_t fin_chi2;        // finalize_grad1 also forms chi^2 (set at launch)
   double *grad_part;       // gradient partials [set][item][nsrc][10]
   void *rho_g;             // float64 gradient: residual tile per work item
                            //   [item][nbt][nc][4] double2

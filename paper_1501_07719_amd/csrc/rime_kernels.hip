@@ -1143,11 +1143,13 @@ __global__ __launch_bounds__(256) void finalize_chi2(const KParams p) {
   chi2_reduce(p, blockIdx.x, scr);
 }
 
-// Level 1: workgroups (source-parameter blocks, item chunks, sets); each thread
+// Level 1: grid (source-parameter blocks, item chunks, sets); each thread
 // sums `grad_chunks` consecutive items of one (source, parameter).  One launch
-// also forms chi^2 (one workgroup per set, in an extra row of chunks) and, with
+// also forms chi^2 (an extra row of chunks, one workgroup per set) and, with
 // the matrix-core adjoint, the first level of the point sources' sums, whose
-// rows the others then leave out.
+// rows the others then leave out (further layers past the sets).  Each
+// dimension of the grid stays within its own limit; one flat dimension for all
+// of them would pass 2^32 threads in batches of many sets.
 //
 // Point sources (partials [sr][item][kPmeSR][7]): thread = one column (source,
 // component) of the partial rows, workgroup = 256 contiguous columns of one
@@ -1180,25 +1182,21 @@ __device__ inline void points_level1(const KParams &p, int bx, int sr, int ch) {
 // First gradient row that level 1 and 2 form from the per-baseline partials.
 __device__ inline int first_row(const KParams &p) { return p.pme_adj ? p.one.npsrc : 0; }
 
-__global__ __launch_bounds__(256) void finalize_grad1(const KParams p, int nblk, int nrow) {
+__global__ __launch_bounds__(256) void finalize_grad1(const KParams p, int nrow) {
   __shared__ double2 scr[256 / kWave];
-  const int nmain = nblk * nrow * p.nset;
-  int b = blockIdx.x;
-  if (b >= nmain) {
-    b -= nmain;
-    if (b < p.fin_chi2) {
-      chi2_reduce(p, b, scr);
-    } else {
-      b -= p.fin_chi2;
-      const int bx = b % (kPmeFinRow / 256);
-      b /= kPmeFinRow / 256;
-      points_level1(p, bx, b % p.pme_nsr, b / p.pme_nsr);
-    }
+  const int bx = blockIdx.x, chunk = blockIdx.y, set = blockIdx.z;
+  if (set >= p.nset) {
+    int b = ((set - p.nset) * static_cast<int>(gridDim.y) + chunk) * static_cast<int>(gridDim.x) +
+            bx;
+    const int px = b % (kPmeFinRow / 256);
+    b /= kPmeFinRow / 256;
+    if (b < p.pme_nsr * p.pme_fchunk) points_level1(p, px, b % p.pme_nsr, b / p.pme_nsr);
     return;
   }
-  const int bx = b % nblk;
-  b /= nblk;
-  const int chunk = b % nrow, set = b / nrow;
+  if (chunk >= nrow) {
+    if (bx == 0 && p.fin_chi2) chi2_reduce(p, set, scr);
+    return;
+  }
   const SetDesc sd = p.sets ? p.sets[set] : p.one;
   const int nsrc = sd.npsrc + sd.ngsrc + sd.nxsrc;
   const int idx = first_row(p) * 10 + bx * 256 + threadIdx.x;
@@ -1458,14 +1456,15 @@ hipError_t launch_finalize(const KParams &p, int mode, int max_nsrc, hipStream_t
     return hipGetLastError();
   }
   KParams q = p;
-  q.fin_chi2 = with_chi2 ? p.nset : 0;
+  q.fin_chi2 = with_chi2 ? 1 : 0;
   const int ext = max_nsrc - (p.pme_adj ? p.one.npsrc : 0);  // rows of the per-baseline partials
-  const int nblk = (ext * 10 + 255) / 256;
+  const int nblk = (ext * 10 + 255) / 256, nrow = nblk > 0 ? p.grad_nchunk : 0;
   const int points = p.pme_adj ? kPmeFinRow / 256 * p.pme_nsr * p.pme_fchunk : 0;
-  const int grid = nblk * p.grad_nchunk * p.nset + q.fin_chi2 + points;
-  if (grid > 0)
-    hipLaunchKernelGGL(finalize_grad1, dim3(grid), dim3(256), 0, stream, q, max(nblk, 1),
-                       nblk > 0 ? p.grad_nchunk : 0);
+  // (the points' workgroups fill layers of gx x gy: 2^15 layers at most)
+  const int gy = max(nrow + q.fin_chi2, 1);
+  const int gx = nblk > 0 && points / (nblk * gy) < (1 << 15) ? nblk : max(nblk, kPmeFinRow / 256);
+  hipLaunchKernelGGL(finalize_grad1, dim3(gx, gy, p.nset + (points + gx * gy - 1) / (gx * gy)),
+                     dim3(256), 0, stream, q, nrow);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(finalize_grad2, dim3((max_nsrc * 10 + 255) / 256, p.nset), dim3(256), 0, stream,

@@ -115,3 +115,26 @@ def test_batch_of_one_set(prec, graph):
         np.testing.assert_array_equal(a[1], b[1])
     batch.close()
     plan.close()
+
+
+def test_many_uneven_sets_in_one_batch():
+    """Sums of a batch whose (largest set) x (chunks) x (sets) launch is past 2^24
+    workgroups: 65100 sets of one source and one of 6600."""
+    obs, sky, D, W = problem(3, 1, 64, 6600, 0, 0, "")
+    big, one = R.DeviceSky.from_host(sky), R.DeviceSky.from_host(sky.subset(1, 0))
+    n = 65100
+    plan = R.Plan(obs)
+    batch = R.Batch(plan, [one] * n + [big])
+    Dd, Wd = dev(D, W)
+    ws = torch.empty(batch.workspace_size(R.MODE_CHI2_GRAD, 0), dtype=torch.uint8, device="cuda")
+    chi2 = torch.full((n + 1,), -1.0, **F64)
+    grad = torch.full((batch.total_src, 10), float("nan"), **F64)
+    R.rime_chi2_batched(batch, 0, Dd, Wd, chi2, grad, ws)
+    torch.cuda.synchronize()
+    c, g = chi2.cpu().numpy(), grad.cpu().numpy()
+    ref = [gradient(obs, s, D, W) for s in (sky.subset(1, 0), sky)]
+    assert (c[:n] == c[0]).all() and (g[:n] == g[0]).all()
+    check((c[0], g[:1]), ref[0], sky.subset(1, 0))
+    check((c[n], g[n:]), ref[1], sky)
+    batch.close()
+    plan.close()
