@@ -149,9 +149,11 @@ void rime_plan_destroy(rime_plan *plan);
 /* Bytes of device workspace that one call of `mode` needs for `nset` sets with
  * `total_src` sources in all (nset = 1 for the single-sky calls, where
  * total_src may be 0; otherwise total_src >= nset).  0 for invalid
- * arguments.  With a float64 forward on large arrays it includes the
- * per-antenna planes of the float64 engine; a call with less, but enough for
- * the per-baseline kernel, is accepted and runs on that kernel. */
+ * arguments.  With a float64 forward on large arrays it includes the float64
+ * engine's per-antenna planes and partial sums of one pass over time (about 2
+ * GiB at most, or one timestep's when that is more).  A workspace for the
+ * largest sky also serves smaller ones.  A call with less, but enough for the
+ * per-baseline kernel, is accepted and runs on that kernel. */
 size_t rime_workspace_size(const rime_plan *plan, rime_mode mode, rime_precision prec,
                            int32_t nset, int64_t total_src);
 
@@ -339,8 +341,9 @@ rime_status rime_variant_info(rime_mode mode, rime_precision prec, int32_t index
  * set, alternating between two streams (workspace: one set's per stream, as
  * rime_batch_workspace_size counts it; rime_workspace_size with the batch's
  * nset and total source count is never smaller).  Large float64 sets also run
- * one by one when the workspace is of rime_batch_workspace_size; with
- * rime_workspace_size bytes all sets share one launch sequence.  For RIME_MIXED_RES64 the
+ * one by one when the workspace holds what that takes, as one of
+ * rime_batch_workspace_size does; with less, all sets share one launch
+ * sequence.  For RIME_MIXED_RES64 the
  * chi-squared variants are the float64 forwards and the gradient variants
  * the float32 adjoints (the forward of a gradient call is the plan's
  * RIME_MODE_CHI2 variant of that precision). */

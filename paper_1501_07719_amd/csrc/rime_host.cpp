@@ -26,6 +26,7 @@ hipError_t launch_planes(const KParams &p, hipStream_t stream);
 hipError_t launch_p64_planes(const KParams &p, hipStream_t stream);
 hipError_t launch_p64_forward(const KParams &p, int mode, hipStream_t stream);
 hipError_t launch_p64_adjoint(const KParams &p, hipStream_t stream);
+hipError_t launch_p64_partials(const KParams &p, bool last, hipStream_t stream);
 hipError_t launch_p64_finalize(const KParams &p, hipStream_t stream);
 int variant_count(int mode, int prec);
 const Variant *variant_info(int mode, int prec, int index);
@@ -364,15 +365,26 @@ bool p64_takes(int mode, const SetDesc &d) {
   return 2 * n >= groups * kWave;
 }
 
-// Upper bound on the planes and residual slots of one time pass of the engine.
-constexpr size_t kP64PassBytes = size_t(24) << 30;
+// What one time pass of the engine may keep in the workspace: the planes, the
+// residual slots and the partial gradients of its timesteps.  Short passes cost
+// launches and a partly idle last round of every kernel, long ones memory (64
+// antennas, 100 timesteps, 64 channels, 1000 points + 500 Gaussians, gradient:
+// 57.4 ms in a workspace of 1.8 GB with passes of 1 GiB, 55.2 in 2.8 GB with 2,
+// 55.9 in 5.0 GB with 4, 55.9 in 16.9 GB with all timesteps at once).  A single
+// timestep may take more, up to kP64StepBytes: its data and the per-baseline
+// kernel's own partial sums are then of that order too.
+constexpr size_t kP64PassBytes = size_t(2) << 30;
+constexpr size_t kP64StepBytes = size_t(24) << 30;
+constexpr int64_t kP64MinSrc = 32, kP64MaxSrc = 1 << 21;
+// bytes of one adjoint item's partial gradients: 10 doubles per lane
+constexpr size_t kP64PartBytes = 10 * kWave * sizeof(double);
 
 struct P64Geometry {
   int nap = 0, ns = 0;     // padded antennas and sources of the planes
   bool k3 = false;         // planes of the beam-gradient factor
   size_t plane_t = 0;      // plane entries per timestep
   size_t rho_t = 0;        // residual slots x 4 per timestep
-  size_t per_t = 0;        // bytes of both
+  size_t step = 0;         // bytes of both, and of the partials of one channel group, per timestep
   int tpass = 1;           // timesteps per pass
   int nr = 4, ntask = 0;   // forward: baselines per lane, tasks
   int tch = 1;             // forward: timesteps per work item
@@ -380,6 +392,11 @@ struct P64Geometry {
   int ncw = 1, ncg = 1;    // adjoint: channels per work item, channel groups
   int64_t nsg_max = 0;     // bound on its groups of 64 sources
   int split = 1;           // parts of a sub-block per work item
+  int64_t npart = 0;       // adjoint work items of a pass
+  // the same bounded over all skies of no more sources and all chunks of no
+  // more timesteps, for the sizes that callers are told
+  size_t step_max = 0;
+  int64_t nitem_max = 0, extra_max = 0;
 };
 
 P64Geometry p64_geometry(const rime_plan *plan, int mode, int64_t total_src) {
@@ -390,40 +407,46 @@ P64Geometry p64_geometry(const rime_plan *plan, int mode, int64_t total_src) {
   g.ns = static_cast<int>((total_src + 7) / 8 * 8);
   g.plane_t = static_cast<size_t>(plan->nchan) * g.ns * g.nap;
   g.rho_t = grad ? static_cast<size_t>(plan->nchan) * plan->npair * kPmeBlk * kPmeBlk * 4 : 0;
-  g.per_t = g.plane_t * (sizeof(double2) + (g.k3 ? sizeof(double) : 0)) +
-            g.rho_t * sizeof(double2);
-  g.tpass = static_cast<int>(
-      std::max<size_t>(1, std::min<size_t>(plan->ntime, kP64PassBytes / g.per_t)));
+  g.nsg_max = total_src / kWave + 3;
+  g.step = g.plane_t * (sizeof(double2) + (g.k3 ? sizeof(double) : 0)) +
+           g.rho_t * sizeof(double2) +
+           (grad ? static_cast<size_t>(g.nsg_max) * plan->nsub * kP64PartBytes : 0);
+  g.step_max = std::min(g.step, kP64StepBytes);
+  // passes of equal length
+  const int64_t fit = std::max<int64_t>(
+      1, std::min<int64_t>(plan->ntime, static_cast<int64_t>(kP64PassBytes / g.step)));
+  const int64_t npass = (plan->ntime + fit - 1) / fit;
+  g.tpass = static_cast<int>((plan->ntime + npass - 1) / npass);
   // four baselines per lane once that gives the chip's 1024 SIMDs two
   // wavefronts each; one per lane below (shorter chains on an idle chip)
   const int64_t w4 = static_cast<int64_t>(plan->ntime) * plan->nchan * plan->ntask4;
   g.nr = w4 >= 2048 ? 4 : 1;
   g.ntask = g.nr == 4 ? plan->ntask4 : plan->ntask1;
+  // about 2^15 forward items per pass
   const int64_t per = static_cast<int64_t>(plan->nchan) * g.ntask;  // items per time chunk
   g.tch = static_cast<int>(std::max<int64_t>(
-      1, std::min<int64_t>(g.tpass, (per * plan->ntime + 32767) / 32768)));
-  int64_t nch = 0;
-  for (int t0 = 0; t0 < plan->ntime; t0 += g.tpass)
-    nch += (std::min(g.tpass, plan->ntime - t0) + g.tch - 1) / g.tch;
-  g.nitem = nch * per;
-  g.nsg_max = total_src / kWave + 3;
-  const int64_t one = g.nsg_max * plan->ntime * plan->nsub;  // items with one channel group
-  const int64_t ncw = std::max<int64_t>(1, std::min<int64_t>(plan->nchan,
-                                                             one * plan->nchan / 65536));
+      1, std::min<int64_t>(g.tpass, (per * g.tpass + 32767) / 32768)));
+  const int64_t tail = plan->ntime - (npass - 1) * g.tpass;  // timesteps of the last pass
+  g.nitem = per * ((npass - 1) * ((g.tpass + g.tch - 1) / g.tch) + (tail + g.tch - 1) / g.tch);
+  // (a pass has at most 2^15 + per items; with one baseline per lane the call
+  // has fewer than 8192)
+  g.nitem_max = std::max<int64_t>(8192, std::min(plan->ntime * per, npass * (32768 + per)));
+  // between 2^16 and 2^17 adjoint items per pass
+  const int64_t one = g.nsg_max * g.tpass * plan->nsub;  // items with one channel group
+  const int64_t ncw =
+      std::max<int64_t>(1, std::min<int64_t>(plan->nchan, one * plan->nchan / 65536));
   g.ncg = static_cast<int>((plan->nchan + ncw - 1) / ncw);
   g.ncw = (plan->nchan + g.ncg - 1) / g.ncg;
   g.ncg = (plan->nchan + g.ncw - 1) / g.ncw;
   // one wavefront's sub-block takes tens of microseconds; eighths of it while
   // that leaves the chip's 2048 resident wavefronts unfilled
-  g.split = g.nsg_max * plan->ntime * g.ncg * plan->nsub < 4096 ? 8 : 1;
+  g.split = one * g.ncg < 4096 ? 8 : 1;
+  g.npart = one * g.ncg * g.split;
+  // items beyond one channel group per timestep: eight times the (at most
+  // 4095) unsplit ones, or up to 2^17
+  const int64_t all = g.nsg_max * plan->ntime * plan->nsub * plan->nchan;
+  g.extra_max = all < 4096 ? 8 * all : std::max<int64_t>(32768, std::min<int64_t>(all, 131072));
   return g;
-}
-
-// Bytes of the adjoint's partial gradients: 10 doubles per lane of each item.
-size_t p64_part_bytes(const rime_plan *plan, const P64Geometry &g, int mode) {
-  if (mode != RIME_MODE_CHI2_GRAD) return 0;
-  return static_cast<size_t>(g.nsg_max) * plan->ntime * g.ncg * plan->nsub * g.split * 10 * kWave *
-         sizeof(double);
 }
 
 // The float64 engine (rime_p64.hip) runs the float64 forward and gradient of
@@ -433,23 +456,19 @@ size_t p64_part_bytes(const rime_plan *plan, const P64Geometry &g, int mode) {
 // launch more costs what the shorter loops save (46 antennas, 4 (timestep,
 // channel), predict: 40 sources 17.4 against 21.4 us, 8 sources 14.3 against
 // 12.1).  The other calls, and calls whose workspace does not hold its planes,
-// run on the per-baseline kernel.
-//
-// A workspace must also stay near what the per-baseline kernel asks for, and
-// the grids within their limits: one timestep's planes and residuals and the
-// partial gradients take at most one pass's bound each, and the planes' and
-// the sums' grid rows (timesteps, channels in fours, groups of 64 sources)
-// stay under 2^16.
-bool p64_active(const rime_plan *plan, const Variant &v, int prec, int nset, int64_t total_src,
-                int mode) {
-  if (prec != RIME_FP64 || nset != 1 || v.threads != 256 || v.nc != 2 || plan->nbl <= 96 ||
-      !plan->pme_adj_ok || total_src < 32)
-    return false;
-  if (plan->ntime > (1 << 15) || plan->nchan > (1 << 17) || total_src > (1 << 21)) return false;
-  const P64Geometry g = p64_geometry(plan, mode, total_src);
-  return g.per_t <= kP64PassBytes && p64_part_bytes(plan, g, mode) <= kP64PassBytes;
+// run on the per-baseline kernel.  The planes' and the sums' grid rows
+// (timesteps, channels in fours, groups of 64 sources) stay under 2^16, and one
+// timestep within kP64StepBytes.
+bool p64_plan_ok(const rime_plan *plan, const Variant &v, int prec, int nset) {
+  return prec == RIME_FP64 && nset == 1 && v.threads == 256 && v.nc == 2 && plan->nbl > 96 &&
+         plan->pme_adj_ok && plan->ntime <= (1 << 15) && plan->nchan <= (1 << 17);
 }
 
+bool p64_active(const rime_plan *plan, const Variant &v, int prec, int nset, int64_t total_src,
+                int mode) {
+  return p64_plan_ok(plan, v, prec, nset) && total_src >= kP64MinSrc && total_src <= kP64MaxSrc &&
+         p64_geometry(plan, mode, total_src).step <= kP64StepBytes;
+}
 
 // Chunks of adjoint items that the first pass of the engine's gradient sums forms.
 constexpr int kP64FinChunks = 64;
@@ -460,15 +479,23 @@ int64_t dom_words(int nset, int64_t total_src) {
   return 1 + static_cast<int64_t>(nset) * std::max<int64_t>(1, (total_src + 255) / 256);
 }
 
+// What a layout is for: a call as it runs, the least that the call can run with
+// (without the float64 engine), or, as the size that callers are told, a bound
+// on the first over all skies of no more sources (and chunks of no more
+// timesteps), so that a workspace for the largest sky serves the smaller ones.
+enum class Need { kCall, kLeast, kBound };
+
 // fwd_sums = false: the point-source sums of the matrix-core forward are not
-// needed (the adjoint half of the float64-residual mode).  lean: the least that
-// the call can run with (without the float64 engine).
+// needed (the adjoint half of the float64-residual mode).
 WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g, int nset,
                    int64_t total_src, const Variant &v, bool fwd_sums = true, int terms = 0,
-                   bool lean = false) {
+                   Need need = Need::kCall) {
   WsLayout L;
-  L.p64 = !lean && p64_active(plan, v, prec, nset, total_src, mode);
-  const P64Geometry pg = L.p64 ? p64_geometry(plan, mode, total_src) : P64Geometry{};
+  const bool bound = need == Need::kBound;
+  L.p64 = bound ? p64_plan_ok(plan, v, prec, nset) && total_src >= kP64MinSrc
+                : need == Need::kCall && p64_active(plan, v, prec, nset, total_src, mode);
+  const P64Geometry pg =
+      L.p64 ? p64_geometry(plan, mode, std::min(total_src, kP64MaxSrc)) : P64Geometry{};
   const bool base = !L.p64;  // regions of the per-baseline kernel
   const size_t r4 = prec == RIME_FP64 ? 32 : 16;
   size_t off = 0;
@@ -478,7 +505,7 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
   off += align_up(static_cast<size_t>(total_src) * sizeof(double4));
   L.lon = off;
   off += align_up(static_cast<size_t>(total_src) * sizeof(double2));
-  const size_t rows = L.p64 ? pg.ns : total_src;
+  const size_t rows = L.p64 ? (total_src + 7) / 8 * 8 : total_src;
   L.st = off;
   off += align_up(rows * plan->nchan * r4);
   L.gs = off;
@@ -489,8 +516,9 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
   }
   L.chi2 = off;
   if (mode != RIME_MODE_PREDICT)
-    off += align_up((L.p64 ? static_cast<size_t>(pg.nitem)
-                           : static_cast<size_t>(nset) * g.items_per_set) *
+    off += align_up(static_cast<size_t>(!L.p64  ? static_cast<int64_t>(nset) * g.items_per_set
+                                        : bound ? pg.nitem_max
+                                                : pg.nitem) *
                     sizeof(double2));
   L.grad = off;
   if (base && mode == RIME_MODE_CHI2_GRAD)
@@ -549,24 +577,33 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
     }
   }
   if (L.p64) {
-    L.p64_a = off;
-    off += align_up(pg.plane_t * pg.tpass * sizeof(double2));
     L.has_k3 = pg.k3;
-    if (pg.k3) {
-      L.p64_k3 = off;
-      off += align_up(pg.plane_t * pg.tpass * sizeof(double));
-    }
     if (mode == RIME_MODE_CHI2_GRAD) {
       L.p64_geo = off;
       off += align_up(static_cast<size_t>(plan->ntime) * plan->npair * kPmeBlk * kPmeBlk *
                       sizeof(double2));
-      L.p64_rho = off;
-      off += align_up(pg.rho_t * pg.tpass * sizeof(double2));
-      L.p64_part = off;
-      off += align_up(p64_part_bytes(plan, pg, mode));
       L.pfin = off;
       off += align_up(static_cast<size_t>(pg.nsg_max) * kP64FinChunks * 10 * kWave *
                       sizeof(double2));
+    }
+    // one pass: planes, residual and partial gradients
+    if (bound) {
+      off += align_up(std::min(plan->ntime * pg.step_max, std::max(kP64PassBytes, pg.step_max)));
+      if (mode == RIME_MODE_CHI2_GRAD) off += pg.extra_max * kP64PartBytes;
+      off += 4 * kAlign;
+    } else {
+      L.p64_a = off;
+      off += align_up(pg.plane_t * pg.tpass * sizeof(double2));
+      if (pg.k3) {
+        L.p64_k3 = off;
+        off += align_up(pg.plane_t * pg.tpass * sizeof(double));
+      }
+      if (mode == RIME_MODE_CHI2_GRAD) {
+        L.p64_rho = off;
+        off += align_up(pg.rho_t * pg.tpass * sizeof(double2));
+        L.p64_part = off;
+        off += align_up(pg.npart * kP64PartBytes);
+      }
     }
   }
   if (terms & TERM_DIE_GRAD) {
@@ -598,12 +635,12 @@ struct Res64Layout {
 
 Res64Layout res64_layout(const rime_plan *plan, int mode, const Variant &vf,
                          const Variant *va, int nset, int64_t total_src, int terms = 0,
-                         bool lean = false) {
+                         Need need = Need::kCall) {
   Res64Layout R;
   // the forward writes the partials of the G gradient; both halves stage the
   // brightness per timestep; the adjoint writes its per-timestep partials
   R.f = ws_layout(plan, RIME_MODE_CHI2, RIME_FP64, geometry(plan, vf, nset), nset, total_src,
-                  vf, true, terms & (TERM_DIE_GRAD | TERM_STOKES_T), lean);
+                  vf, true, terms & (TERM_DIE_GRAD | TERM_STOKES_T), need);
   size_t off = R.f.total;
   if (mode == RIME_MODE_CHI2_GRAD && va) {
     R.va = *va;
@@ -622,24 +659,23 @@ Res64Layout res64_layout(const rime_plan *plan, int mode, const Variant &vf,
 }
 
 // Workspace of one call of (mode, prec) with kernel variant `vidx` and, for a
-// gradient in the float64-residual mode, forward variant `fidx`; lean: the
-// least that the call accepts.
+// gradient in the float64-residual mode, forward variant `fidx`: the least that
+// the call accepts (lean), or what it and calls with smaller skies run best with.
 size_t call_ws(const rime_plan *plan, int mode, int prec, int vidx, int fidx, int nset,
                int64_t total_src, int terms = 0, bool lean = false) {
-  size_t best = 0;
   const Variant *v = variant_info(mode, prec, vidx);
   if (!v) return 0;
-  if (!lean)  // a call may also run without the engine, whatever its sky
-    best = call_ws(plan, mode, prec, vidx, fidx, nset, total_src, terms, true);
-  if (prec != kRes64)
-    return std::max(best, ws_layout(plan, mode, prec, geometry(plan, *v, nset), nset, total_src, *v,
-                                    true, terms, lean)
-                              .total);
-  if (mode == RIME_MODE_CHI2)
-    return std::max(best, res64_layout(plan, mode, *v, nullptr, nset, total_src, terms, lean).total);
-  const Variant *vf = variant_info(RIME_MODE_CHI2, kRes64, fidx);
+  const bool res = prec == kRes64, grad = mode == RIME_MODE_CHI2_GRAD;
+  const Variant *vf = res && grad ? variant_info(RIME_MODE_CHI2, kRes64, fidx) : v;
   if (!vf) return 0;
-  return std::max(best, res64_layout(plan, mode, *vf, v, nset, total_src, terms, lean).total);
+  auto bytes = [&](Need need) {
+    if (res) return res64_layout(plan, mode, *vf, grad ? v : nullptr, nset, total_src, terms, need).total;
+    return ws_layout(plan, mode, prec, geometry(plan, *v, nset), nset, total_src, *v, true, terms,
+                     need)
+        .total;
+  };
+  const size_t least = bytes(Need::kLeast);
+  return lean ? least : std::max(least, bytes(Need::kBound));
 }
 
 // Whether a batched call with this variant runs the single-sky pipeline once
@@ -892,7 +928,7 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
       p.p64_nsg = (c.one.npsrc + kWave - 1) / kWave + (c.one.ngsrc + kWave - 1) / kWave +
                   (c.one.nxsrc + kWave - 1) / kWave;
       p.pme_fchunk = static_cast<int>(std::min<int64_t>(
-          kP64FinChunks, static_cast<int64_t>(plan->ntime) * pg.ncg * plan->nsub * pg.split));
+          kP64FinChunks, static_cast<int64_t>(pg.tpass) * pg.ncg * plan->nsub * pg.split));
       p.p64_split = pg.split;
     }
   } else if (c.grad_stokes_t && c.mode == RIME_MODE_CHI2_GRAD)
@@ -936,11 +972,13 @@ KParams make_params(const rime_plan *plan, const Call &c, const Variant &v, cons
 
 // The float64 engine's kernels, in passes over time: planes, forward (kernel
 // mode `fmode`: the call's mode, or 3 for the float64-residual forward) and,
-// for a gradient, the adjoint.
-rime_status enqueue_p64(const rime_plan *plan, KParams p, int mode, int fmode, int64_t total_src,
+// for a gradient, the adjoint, whose partials are summed before the next pass
+// overwrites them.  Those of the last pass (p's on return) are left to the caller.
+rime_status enqueue_p64(const rime_plan *plan, KParams &p, int mode, int fmode, int64_t total_src,
                         hipStream_t stream) {
   const P64Geometry pg = p64_geometry(plan, mode, total_src);
   for (int t0 = 0; t0 < plan->ntime; t0 += pg.tpass) {
+    if (t0 > 0 && mode == RIME_MODE_CHI2_GRAD) RIME_HIP(launch_p64_partials(p, false, stream));
     p.pme_t0 = t0;
     p.pme_nt = std::min(pg.tpass, plan->ntime - t0);
     RIME_HIP(launch_p64_planes(p, stream));
@@ -976,7 +1014,7 @@ rime_status enqueue_res64(const rime_plan *plan, const Call &c, int vidx, void *
   if (!vf || (grad && !va)) return RIME_ERR_UNSUPPORTED;
   Res64Layout R = res64_layout(plan, c.mode, *vf, va, c.nset, c.total_src, c.terms());
   if (ws_bytes < R.total)
-    R = res64_layout(plan, c.mode, *vf, va, c.nset, c.total_src, c.terms(), true);
+    R = res64_layout(plan, c.mode, *vf, va, c.nset, c.total_src, c.terms(), Need::kLeast);
   if (!ws || ws_bytes < R.total) return RIME_ERR_WORKSPACE;
   const Geometry gf = geometry(plan, *vf, c.nset);
   const Geometry ga = grad ? geometry(plan, R.va, c.nset) : Geometry{};
@@ -1049,7 +1087,7 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
   const Geometry g = geometry(plan, *v, c.nset);
   WsLayout L = ws_layout(plan, mode, prec, g, c.nset, c.total_src, *v, true, c.terms());
   if (ws_bytes < L.total || (L.p64 && !p64_takes(mode, c.one)))
-    L = ws_layout(plan, mode, prec, g, c.nset, c.total_src, *v, true, c.terms(), true);
+    L = ws_layout(plan, mode, prec, g, c.nset, c.total_src, *v, true, c.terms(), Need::kLeast);
   if (L.total > 0 && (!ws || ws_bytes < L.total)) return RIME_ERR_WORKSPACE;
   const int64_t nitems = static_cast<int64_t>(c.nset) * g.items_per_set;
   if (nitems <= 0 || nitems > 0x7fffffff) return RIME_ERR_UNSUPPORTED;
@@ -1084,10 +1122,12 @@ rime_status enqueue(const rime_plan *plan, const Call &c, int vidx, void *ws, si
     if (st != RIME_OK) return st;
   }
   if (events && plan->ev_stop) RIME_HIP(hipEventRecord(plan->ev_stop, stream));
-  if (L.p64 && mode == RIME_MODE_CHI2_GRAD)
+  if (L.p64 && mode == RIME_MODE_CHI2_GRAD) {
+    RIME_HIP(launch_p64_partials(p, true, stream));
     RIME_HIP(launch_p64_finalize(p, stream));
-  else
+  } else {
     RIME_HIP(launch_finalize(p, mode, c.max_nsrc, stream, true));
+  }
   if (p.die_part) RIME_HIP(launch_die_grad(p, stream));
   if (p.gst_part) RIME_HIP(launch_stokes_t_grad(p, stream));
   return RIME_OK;
@@ -1157,7 +1197,7 @@ rime_plan sub_plan(const rime_plan *plan, int t0, int nt) {
 struct StreamLayout {
   int chunk_t = 0, nchunk = 0;
   size_t dbytes_t = 0, wbytes_t = 0;   // data and weight bytes per timestep
-  size_t hdr = 0, stage[2] = {0, 0}, wstage = 0, part = 0, chunk_off = 0, chunk_ws = 0;
+  size_t hdr = 0, stage[2] = {0, 0}, wstage = 0, part = 0, chunk_off = 0;
   int64_t stride = 0;                  // doubles per chunk result (chi^2, gradient)
   size_t total = 0;
 };
@@ -1185,10 +1225,15 @@ StreamLayout stream_layout(const rime_plan *plan, int mode, int prec, int64_t ns
   S.part = off;
   off += align_up(static_cast<size_t>(S.nchunk) * S.stride * sizeof(double));
   S.chunk_off = off;
-  const rime_plan sp = sub_plan(plan, 0, S.chunk_t);
-  S.chunk_ws = align_up(ws_max(&sp, mode, prec, 1, nsrc, lean));
-  off += S.chunk_ws;
-  S.total = off;
+  // (a call accepts what a full chunk needs; the size that callers are told
+  // covers a shorter last chunk, whose launch geometry may need more)
+  rime_plan sp = sub_plan(plan, 0, S.chunk_t);
+  size_t chunk_ws = ws_max(&sp, mode, prec, 1, nsrc, lean);
+  if (!lean && plan->ntime % S.chunk_t) {
+    sp.ntime = plan->ntime % S.chunk_t;
+    chunk_ws = std::max(chunk_ws, ws_max(&sp, mode, prec, 1, nsrc));
+  }
+  S.total = off + align_up(chunk_ws);
   return S;
 }
 
@@ -1744,7 +1789,8 @@ rime_status rime_chi2_streamed(const rime_plan *plan, const rime_sky *sky, rime_
     cc.weight = dst + S.wstage;
     cc.chi2 = part + k * S.stride;
     cc.grad = grad ? part + k * S.stride + 1 : nullptr;
-    st = enqueue(&sp, cc, plan->variant[mode][prec], w + S.chunk_off, S.chunk_ws, s, false);
+    st = enqueue(&sp, cc, plan->variant[mode][prec], w + S.chunk_off, ws_bytes - S.chunk_off, s,
+                 false);
     if (st == RIME_OK && (e = hipEventRecord(plan->ev_done[b], s)) != hipSuccess)
       st = hip_fail(e);
   }

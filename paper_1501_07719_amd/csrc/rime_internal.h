@@ -174,7 +174,7 @@ struct KParams {
   int64_t p64_item0;                   // first chi^2 partial of this pass
   int32_t p64_ncw, p64_ncg, p64_nsg;   // adjoint: channels per item, groups, source groups
   int32_t p64_split;                   // parts of a sub-block (1, or 8 in small calls)
-  double *p64_part;        // [nsg][ntime][ncg][nsub][split][10][64] gradient partials
+  double *p64_part;        // [nsg][pme_nt][ncg][nsub][split][10][64] gradient partials
 };
 
 // Antenna block of the matrix-core engine (rows and columns of one MFMA tile),

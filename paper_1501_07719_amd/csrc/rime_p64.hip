@@ -648,17 +648,18 @@ __global__ __launch_bounds__(256, 2) void p64_adjoint(const KParams p) {
   }
   // partials [source group][timestep][channel group][sub-block part][10][64]
   double *dst = p.p64_part +
-                (((static_cast<int64_t>(sgr) * p.ntime + t) * p.p64_ncg + cg) * nit + isub) *
-                    (10 * kWave) +
+                (((static_cast<int64_t>(sgr) * p.pme_nt + t - p.pme_t0) * p.p64_ncg + cg) * nit +
+                 isub) * (10 * kWave) +
                 lane;
 #pragma unroll
   for (int i = 0; i < 10; ++i) dst[i * kWave] = s_lds[wave].grad[i][lane];
 }
 
-// Gradient rows from the adjoint partials, in two passes with a fixed order:
-// thread = one column (parameter, source) of a chunk of items, then thread =
-// (source, parameter) over the chunks.
-// The first launch also forms chi^2, in an extra row of workgroups.
+// Gradient rows from the adjoint partials, with a fixed order: after each pass
+// over time, thread = one column (parameter, source) of a chunk of the pass's
+// items, added to what the earlier passes left; at the end thread = (source,
+// parameter) over the chunks.  The first launch after the last pass also forms
+// chi^2, in an extra row of workgroups.
 __global__ __launch_bounds__(256) void p64_fin_items(const KParams p) {
   constexpr int kRow = 10 * kWave;
   __shared__ double2 scr[256 / kWave];
@@ -669,11 +670,16 @@ __global__ __launch_bounds__(256) void p64_fin_items(const KParams p) {
   }
   const int col = blockIdx.x * 256 + threadIdx.x;
   if (col >= kRow) return;
-  const int64_t nper = static_cast<int64_t>(p.ntime) * p.p64_ncg * p.nsub * p.p64_split;
+  const int64_t nper = static_cast<int64_t>(p.pme_nt) * p.p64_ncg * p.nsub * p.p64_split;
   const int64_t cs = (nper + p.pme_fchunk - 1) / p.pme_fchunk;
   const int64_t i1 = min(nper, (ch + 1) * cs);
   const double *src = p.p64_part + static_cast<int64_t>(sg) * nper * kRow + col;
+  double2 *sum = p.pfin + (static_cast<int64_t>(sg) * p.pme_fchunk + ch) * kRow + col;
   Comp acc;
+  if (p.pme_t0 > 0) {
+    const double2 v = *sum;
+    acc.merge(v.x, v.y);
+  }
   int64_t i = ch * cs;
   for (; i + 8 <= i1; i += 8) {
     double v[8];
@@ -683,7 +689,7 @@ __global__ __launch_bounds__(256) void p64_fin_items(const KParams p) {
     for (int k = 0; k < 8; ++k) acc.add(v[k]);
   }
   for (; i < i1; ++i) acc.add(src[i * kRow]);
-  p.pfin[(static_cast<int64_t>(sg) * p.pme_fchunk + ch) * kRow + col] = make_double2(acc.s, acc.c);
+  *sum = make_double2(acc.s, acc.c);
 }
 
 __global__ __launch_bounds__(256) void p64_finalize(const KParams p) {
@@ -711,16 +717,17 @@ __global__ __launch_bounds__(256) void p64_finalize(const KParams p) {
   p.grad_out[static_cast<int64_t>(tl.s0 + s) * 10 + j] = 2.0 * (r.s + r.c);
 }
 
-// Gradient of the brightness per timestep from the same partials.
+// Gradient of the brightness per timestep of the pass from the same partials.
 __global__ __launch_bounds__(256) void p64_stokes_t(const KParams p) {
   const SrcTile tl = src_tile(p.one, blockIdx.y, kWave, (p.one.npsrc + kWave - 1) / kWave,
                               (p.one.ngsrc + kWave - 1) / kWave);
-  const int t = blockIdx.x;
+  const int t = p.pme_t0 + blockIdx.x;
   const int k = threadIdx.x / kWave, s = threadIdx.x % kWave;
   if (s >= tl.cnt) return;
   const int nit = p.p64_ncg * p.nsub * p.p64_split;
   const double *src = p.p64_part +
-                      (static_cast<int64_t>(blockIdx.y) * p.ntime + t) * nit * (10 * kWave) +
+                      (static_cast<int64_t>(blockIdx.y) * p.pme_nt + blockIdx.x) * nit *
+                          (10 * kWave) +
                       (2 + k) * kWave + s;
   Comp acc;
   int i = 0;
@@ -799,18 +806,22 @@ hipError_t launch_p64_adjoint(const KParams &p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_p64_finalize(const KParams &p, hipStream_t stream) {
-  const dim3 g1((10 * kWave + 255) / 256, static_cast<unsigned>(p.p64_nsg + 1),
-                static_cast<unsigned>(p.pme_fchunk));
-  hipLaunchKernelGGL(p64_fin_items, g1, dim3(256), 0, stream, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const dim3 g2((10 * kWave + 255) / 256, static_cast<unsigned>(p.p64_nsg));
-  hipLaunchKernelGGL(p64_finalize, g2, dim3(256), 0, stream, p);
-  if ((e = hipGetLastError()) != hipSuccess || !p.grad_stokes_t) return e;
+// Sums of the partials of the pass just done; last: chi^2 too.
+hipError_t launch_p64_partials(const KParams &p, bool last, hipStream_t stream) {
+  const dim3 g((10 * kWave + 255) / 256, static_cast<unsigned>(p.p64_nsg + (last ? 1 : 0)),
+               static_cast<unsigned>(p.pme_fchunk));
+  hipLaunchKernelGGL(p64_fin_items, g, dim3(256), 0, stream, p);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !p.grad_stokes_t) return e;
   hipLaunchKernelGGL(p64_stokes_t,
-                     dim3(static_cast<unsigned>(p.ntime), static_cast<unsigned>(p.p64_nsg)),
+                     dim3(static_cast<unsigned>(p.pme_nt), static_cast<unsigned>(p.p64_nsg)),
                      dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_p64_finalize(const KParams &p, hipStream_t stream) {
+  const dim3 g((10 * kWave + 255) / 256, static_cast<unsigned>(p.p64_nsg));
+  hipLaunchKernelGGL(p64_finalize, g, dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

@@ -4,7 +4,7 @@ the resident single-sky call where both run on the engine."""
 import numpy as np
 import pytest
 
-from rime_synth import Observation
+from rime_synth import Observation, make_problem, random_die, stokes_per_time
 from tests._helpers import TOL, grad_errors, rel
 from tests.test_gpu_p64 import problem
 
@@ -138,3 +138,154 @@ def test_many_uneven_sets_in_one_batch():
     check((c[n], g[n:]), ref[1], sky)
     batch.close()
     plan.close()
+
+
+def engine_sizes(na, ntime, nchan, counts, prec, mode):
+    obs = make_problem("c1", ntime=ntime, nchan=nchan, npsrc=4, ngsrc=0, na=na, key=95,
+                       dense=False).obs
+    plan = R.Plan(obs)
+    out = [plan.workspace_size(mode, prec, 1, n) for n in counts]
+    plan.close()
+    return out
+
+
+@pytest.mark.parametrize("mode,prec", [(0, 0), (1, 0), (2, 0), (1, 2), (2, 2)])
+@pytest.mark.parametrize("na,ntime,nchan", [(64, 1, 64), (20, 7, 5), (64, 3, 17), (33, 50, 3)])
+def test_workspace_grows_with_the_sky(mode, prec, na, ntime, nchan):
+    """A workspace for the largest sky holds what smaller ones take."""
+    counts = [1, 31, 32, 33, 63, 64, 65, 100, 128, 192, 193, 250, 256, 300, 500, 511, 512, 700,
+              1000, 2000, 5000]
+    sizes = engine_sizes(na, ntime, nchan, counts, prec, mode)
+    assert all(a <= b for a, b in zip(sizes, sizes[1:])), list(zip(counts, sizes))
+
+
+def test_ragged_streamed_chunk_runs_on_the_engine():
+    """64 antennas, 64 channels: a chunk of two timesteps takes fewer partial
+    sums than the last chunk of one.  Streamed sums equal those of the two
+    resident calls bit by bit."""
+    obs, sky, D, W = problem(64, 3, 64, 64, 36, 0, "")
+    plan = R.Plan(obs)
+    n = R.rime_streamed_workspace_size(plan, R.MODE_CHI2_GRAD, 0, sky.nsrc, 2)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    chi2, grad = torch.empty(1, **F64), torch.empty((sky.nsrc, 10), **F64)
+    R.rime_chi2_streamed(plan, R.DeviceSky.from_host(sky), 0, torch.as_tensor(D).pin_memory(),
+                         torch.as_tensor(W).pin_memory(), chi2, grad, 2, ws)
+    torch.cuda.synchronize()
+    plan.close()
+    a, b = (gradient(obs.time_slice(t0, t1), sky, np.ascontiguousarray(D[t0:t1]),
+                     np.ascontiguousarray(W[t0:t1])) for t0, t1 in ((0, 2), (2, 3)))
+    assert chi2.item() == a[0] + b[0]
+    np.testing.assert_array_equal(grad.cpu().numpy(), a[1] + b[1])
+
+
+@pytest.mark.parametrize("prec", [0, 2])
+def test_smaller_skies_in_a_workspace_for_the_largest(prec):
+    """A workspace and batch lanes sized by the largest sky run the smaller ones
+    on the same kernels as a workspace of their own: results bit by bit."""
+    obs, sky, D, W = problem(64, 1, 64, 256, 256, 0, "")
+    skies = [sky.subset(a, b) for a, b in ((256, 256), (192, 192), (64, 64), (50, 40))]
+    plan = R.Plan(obs)
+    n = plan.workspace_size(R.MODE_CHI2_GRAD, prec, 1, skies[0].nsrc)
+    own = [gradient(obs, s, D, W, prec=prec) for s in skies]
+    for s, b in zip(skies, own):
+        a = gradient(obs, s, D, W, prec=prec, ws_bytes=n)
+        assert a[0] == b[0]
+        np.testing.assert_array_equal(a[1], b[1])
+    Dd, Wd = dev(D, W, prec)
+    batch = R.Batch(plan, [R.DeviceSky.from_host(s) for s in skies])
+    ws = torch.empty(batch.workspace_size(R.MODE_CHI2_GRAD, prec), dtype=torch.uint8,
+                     device="cuda")
+    chi2 = torch.empty(len(skies), **F64)
+    grad = torch.empty((batch.total_src, 10), **F64)
+    R.rime_chi2_batched(batch, prec, Dd, Wd, chi2, grad, ws)
+    torch.cuda.synchronize()
+    g, at = grad.cpu().numpy(), 0
+    for i, (s, b) in enumerate(zip(skies, own)):
+        assert chi2[i].item() == b[0]
+        np.testing.assert_array_equal(g[at:at + s.nsrc], b[1])
+        at += s.nsrc
+    batch.close()
+    plan.close()
+
+
+def smallest_workspace(call, full):
+    """Least bytes that `call(ws)` accepts."""
+    lo, hi = 0, full  # refused, accepted
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            call(torch.empty(mid, dtype=torch.uint8, device="cuda"))
+            hi = mid
+        except R.RimeError as e:
+            assert e.status == 2
+            lo = mid
+    return hi
+
+
+@pytest.mark.parametrize("na,ntime,nchan,npsrc,ng,engine", [
+    (15, 1, 2, 32, 0, True), (33, 3, 4, 64, 40, True), (64, 9, 9, 33, 41, True),
+    (64, 9, 9, 33, 30, False),
+    (15, 1, 2, 31, 0, False), (14, 2, 2, 64, 0, False)])
+def test_route_of_the_gradient(na, ntime, nchan, npsrc, ng, engine):
+    """The engine's sums and the per-baseline kernel's differ in their last bits:
+    a call with the least workspace it accepts (never the engine) gives other
+    bits exactly when the full workspace takes the engine.  From 32 sources on,
+    lanes half full, over more than 96 baselines."""
+    obs, sky, D, W = problem(na, ntime, nchan, npsrc, ng, 0, "")
+    plan = R.Plan(obs)
+    ds, (Dd, Wd) = R.DeviceSky.from_host(sky), dev(D, W)
+    chi2, grad = torch.empty(1, **F64), torch.empty((sky.nsrc, 10), **F64)
+    call = lambda ws: R.rime_chi2_grad(plan, ds, 0, Dd, Wd, chi2, grad, ws)  # noqa: E731
+    full = plan.workspace_size(R.MODE_CHI2_GRAD, 0, 1, sky.nsrc)
+    least = smallest_workspace(call, full)
+    out = []
+    for n in (full, least):
+        call(torch.empty(n, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        out.append((chi2.item(), grad.cpu().numpy()))
+    plan.close()
+    check(*out, sky)
+    assert np.array_equal(out[0][1], out[1][1]) != engine
+
+
+@pytest.mark.parametrize("prec", [0, 2])
+@pytest.mark.parametrize("terms", [False, True])
+def test_passes_over_time_and_channel_groups(prec, terms):
+    """1400 sources over 64 antennas, 64 channels and 17 timesteps: two passes
+    over time (9 and 8 timesteps), several channels per adjoint item; against
+    the per-baseline kernel (float64-residual: the forward variant)."""
+    obs, sky, D, W = problem(64, 17, 64, 700, 500, 200, "")
+    rng = np.random.default_rng(6)
+    extra = {}
+    if terms:
+        extra = dict(die=torch.as_tensor(random_die(17, 64, 64, rng), device="cuda"),
+                     stokes_t=torch.as_tensor(stokes_per_time(sky, 17, rng), device="cuda"))
+    Dd, Wd = dev(D, W, prec)
+    ds = R.DeviceSky.from_host(sky)
+    out = []
+    for vi in (1, 0):
+        plan = R.Plan(obs)
+        plan.set_variant(R.MODE_CHI2_GRAD if prec == 0 else R.MODE_CHI2, prec, vi)
+        chi2, grad = torch.empty(1, **F64), torch.full((sky.nsrc, 10), float("nan"), **F64)
+        g = {f"grad_{k}": torch.full_like(v, float("nan")) for k, v in extra.items()}
+        n = R.rime_workspace_size_ex(plan, R.MODE_CHI2_GRAD, prec, sky.nsrc,
+                                     **{k: True for k in (*extra, *g)})
+        ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+        R.rime_chi2_ex(plan, ds, prec, Dd, Wd, chi2, grad, ws, **extra, **g)
+        torch.cuda.synchronize()
+        out.append((chi2.item(), grad.cpu().numpy(), {k: v.cpu().numpy() for k, v in g.items()}))
+        plan.close()
+    a, b = out
+    # (the adjoint of the float64-residual mode is float32 in both)
+    tol = TOL[prec]
+    assert rel(a[0], b[0]) <= TOL[0]
+    assert max(grad_errors(a[1], b[1], sky.npsrc).values()) <= tol
+    for k in a[2]:
+        assert np.linalg.norm(a[2][k] - b[2][k]) <= tol * np.linalg.norm(b[2][k]), k
+
+
+def test_workspace_of_the_engine_is_bounded():
+    """64 antennas, 100 timesteps, 64 channels, 1500 sources, gradient: planes
+    of all timesteps take 15 GB; a call asks for one pass over time."""
+    n, = engine_sizes(64, 100, 64, [1500], 0, R.MODE_CHI2_GRAD)
+    assert n <= 3 << 30
