@@ -55,22 +55,24 @@ __global__ __launch_bounds__(256) void p64_planes(const KParams p) {
   const int64_t o = static_cast<int64_t>(tt) * p.nchan * plane + idx;
   double2 *pa = p.p64_a + o;
   double *pk = p.p64_k3 + o;
-  // antennas past the array, and those without baselines, whose coordinates
-  // may be undefined: the adjoint weights their terms with sums of zero
-  if (a >= p.na || p.ant_off[a] == p.ant_off[a + 1]) {
+  if (a >= p.na) {
     for (int c = cb; c < ce; ++c) {
       pa[c * plane] = make_double2(0.0, 0.0);
       if (WITH_K3) pk[c * plane] = 0.0;
     }
     return;
   }
+  // an antenna without baselines may have undefined coordinates, and the
+  // adjoint weights its terms with sums of zero: the origin stands for it
+  const bool held = p.ant_off[a] != p.ant_off[a + 1];
+  auto at = [&](double x) { return held ? x : 0.0; };
   const double4 g = p.src_geo[s];
   const double *x = p.uvw + (static_cast<int64_t>(t) * p.na + a) * 3;
-  const PhaseArg<true> tau(x[0], x[1], x[2], g.x, g.y, g.z);
+  const PhaseArg<true> tau(at(x[0]), at(x[1]), at(x[2]), g.x, g.y, g.z);
   double r2b = 0.0, rb = 0.0;
   if (p.beam) {
     const double *q = p.pointing + (static_cast<int64_t>(t) * p.na + a) * 2;
-    r2b = sumsq_rn(g.x - q[0], g.y - q[1]);
+    r2b = sumsq_rn(g.x - at(q[0]), g.y - at(q[1]));
     rb = sqrt(r2b);
   }
   for (int c = cb; c < ce; ++c) {
@@ -380,6 +382,14 @@ struct AdjLds {
   double grad[10][kWave];
 };
 
+// The value of x in one lane (wavefront-uniform index).
+__device__ inline double lane_value(double x, int lane) {
+  const int64_t b = __double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(b), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
+  return __longlong_as_double(static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo));
+}
+
 template <int SHAPE, bool ST>
 __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, int cg, int s,
                                     AdjLds &lds) {
@@ -391,24 +401,34 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
   const int2 blk = p.pair_blk[pair];
   const int P0 = __builtin_amdgcn_readfirstlane(blk.x) * kPmeBlk + si * 16;
   const int Q0 = __builtin_amdgcn_readfirstlane(blk.y) * kPmeBlk + sj * 16;
-  // row masks, one per lane; the coordinates of antennas without baselines
-  // (and past the array) count as zero.  The coordinates are taken from the
-  // first row's antenna that holds a baseline here: only differences enter,
-  // and an offset common to all antennas would otherwise cost digits in the
-  // difference of the row and column sums
+  // row masks, one per lane.  The coordinates of the 16 + 16 antennas are taken
+  // from the first row's antenna that holds a baseline here: only differences
+  // enter, and an offset common to all antennas would otherwise cost digits in
+  // the difference of the row and column sums.  Antennas without a baseline
+  // here (past the array, or with undefined coordinates) count as zero.
   const uint32_t maskv = p.pair_mask[pair * kPmeBlk + si * 16 + (lane & 15)];
-  const uint64_t rows = __ballot(((maskv >> (sj * 16)) & 0xffffu) != 0u);
-  const double *x0 = p.uvw + (static_cast<int64_t>(t) * p.na + P0 +
-                              __builtin_amdgcn_readfirstlane(__builtin_ctzll(rows))) * 3;
-  if (lane < 32) {
-    const int i = lane < 16 ? P0 + lane : Q0 + lane - 16, a = min(i, p.na - 1);
-    const bool held = i == a && p.ant_off[a] != p.ant_off[a + 1];
+  {
+    const int a = min((lane & 16 ? Q0 : P0) + (lane & 15), p.na - 1);
     const double *x = p.uvw + (static_cast<int64_t>(t) * p.na + a) * 3;
     const double *q = p.pointing + (static_cast<int64_t>(t) * p.na + a) * 2;
+    const double u = x[0], v = x[1], w = x[2], ql = q[0], qm = q[1];
+    const uint32_t row = (maskv >> (sj * 16)) & 0xffffu;
+    const uint32_t rows = static_cast<uint32_t>(__ballot(row != 0u)) & 0xffffu;
+    // OR over each 16 lanes (rotations by 1, 2, 4 and 8 of a DPP row)
+    int cols = static_cast<int>(row);
+    cols |= __builtin_amdgcn_mov_dpp(cols, 0x121, 0xf, 0xf, true);
+    cols |= __builtin_amdgcn_mov_dpp(cols, 0x122, 0xf, 0xf, true);
+    cols |= __builtin_amdgcn_mov_dpp(cols, 0x124, 0xf, 0xf, true);
+    cols |= __builtin_amdgcn_mov_dpp(cols, 0x128, 0xf, 0xf, true);
+    const int first = __builtin_ctz(rows);
+    const double u0 = lane_value(u, first), v0 = lane_value(v, first), w0 = lane_value(w, first);
+    const bool held = ((lane & 16 ? static_cast<uint32_t>(cols) : rows) >> (lane & 15)) & 1u;
     const double2 zero = make_double2(0.0, 0.0);
-    lds.ant[lane][0] = held ? make_double2(x[0] - x0[0], x[1] - x0[1]) : zero;
-    lds.ant[lane][1] = held ? make_double2(x[2] - x0[2], 0.0) : zero;
-    lds.ant[lane][2] = held ? make_double2(q[0], q[1]) : zero;
+    if (lane < 32) {
+      lds.ant[lane][0] = held ? make_double2(u - u0, v - v0) : zero;
+      lds.ant[lane][1] = held ? make_double2(w - w0, 0.0) : zero;
+      lds.ant[lane][2] = held ? make_double2(ql, qm) : zero;
+    }
   }
   const int64_t plane = static_cast<int64_t>(p.nap) * p.p64_ns;
   const int64_t slot0 = static_cast<int64_t>(pair) * (kPmeBlk * kPmeBlk) + si * 16 * kPmeBlk +
