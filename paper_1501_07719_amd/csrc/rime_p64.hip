@@ -110,6 +110,15 @@ __device__ inline void wait_lgkm() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// Between LDS accesses of a wavefront's lanes to each other's data.  The
+// hardware keeps a wavefront's LDS accesses in order; this keeps the compiler
+// from reordering them.  No instruction.
+__device__ inline void lane_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Source sums over [s0, s1) (one morphology) of this lane's NR baselines.  The
 // antenna terms of four sources at a time go from the planes (one 16-byte load
 // per lane and side) through the wavefront's own LDS buffers, two chunks ahead;
@@ -135,8 +144,10 @@ __device__ inline void p64_sweep(const KParams &p, const double2 *pp, const doub
     xq = pq[o];
   };
   auto put = [&](int buf) {
+    lane_exchange();
     s_a[buf][ls][la] = xp;
     s_a[buf][ls][16 + la] = xq;
+    lane_exchange();
   };
   // brightness by (channel, source): the next source's lies in the same cache line
   const RIME_CONST Quad<double> *st =
@@ -429,6 +440,7 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
       lds.ant[lane][1] = held ? make_double2(w - w0, 0.0) : zero;
       lds.ant[lane][2] = held ? make_double2(ql, qm) : zero;
     }
+    lane_exchange();
   }
   const int64_t plane = static_cast<int64_t>(p.nap) * p.p64_ns;
   const int64_t slot0 = static_cast<int64_t>(pair) * (kPmeBlk * kPmeBlk) + si * 16 * kPmeBlk +
@@ -495,8 +507,10 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
         if (SHAPE != SHAPE_POINT) xg = geo[o];
       };
       auto put = [&](int buf) {
+        lane_exchange();
         (&lds.rho[buf][0][0][0])[lane] = xr;
         if (SHAPE != SHAPE_POINT && lane < 16) (&lds.geo[buf][0][0])[lane] = xg;
+        lane_exchange();
       };
       double2 aq[NQ];
       double colR[NQ], colI[NQ];
