@@ -358,7 +358,8 @@ int32_t rime_get_variant(const rime_plan *plan, rime_mode mode, rime_precision p
  * per-baseline kernel and, with a matrix-core variant, the point-source
  * kernels; the small per-source preparation and final-reduction kernels fall
  * outside), rime_plan_set_main_events around the per-baseline kernel (or the
- * float64 engine) alone.
+ * float64 engine's planes, forward and adjoint) alone.  In a batched call that
+ * runs set by set both bracket the whole sequence.
  * NULL turns a hook off.  Used to time the kernels in isolation. */
 rime_status rime_plan_set_timing_events(rime_plan *plan, void *start, void *stop);
 rime_status rime_plan_set_main_events(rime_plan *plan, void *start, void *stop);

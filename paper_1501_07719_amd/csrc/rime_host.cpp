@@ -1970,13 +1970,14 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
     }
     // matrix-core variant or float64 engine: the single-sky pipeline per set,
     // set i in lane i % lanes with that lane's part of the workspace (after
-    // the batch's domain header); the timing events (if any) bracket the whole
-    // sequence on the caller's stream
+    // the batch's domain header); the timing and main events (if any) bracket
+    // the whole sequence on the caller's stream
     const size_t hdr = align_up(static_cast<size_t>(batch_dom_words(b)) * sizeof(int32_t));
     const size_t lane_bytes =
         align_up(call_ws(plan, mode, prec, vidx, fidx, 1, b->max_nsrc, 0, lean));
     const int32_t nwords = static_cast<int32_t>(batch_dom_words(b) - 1);
     if (plan->ev_start) RIME_HIP(hipEventRecord(plan->ev_start, s));
+    if (plan->ev_main0) RIME_HIP(hipEventRecord(plan->ev_main0, s));
     if (lanes > 1) {
       RIME_HIP(hipEventRecord(b->fork, s));
       RIME_HIP(hipStreamWaitEvent(b->lane, b->fork, 0));
@@ -2010,6 +2011,7 @@ rime_status rime_chi2_batched(rime_batch *b, rime_precision prec, const void *da
       if (st == RIME_OK && e2 != hipSuccess) return hip_fail(e2);
     }
     if (st != RIME_OK) return st;
+    if (plan->ev_main1) RIME_HIP(hipEventRecord(plan->ev_main1, s));
     if (plan->ev_stop) RIME_HIP(hipEventRecord(plan->ev_stop, s));
     return RIME_OK;
   };

@@ -225,8 +225,10 @@ class Plan:
                "rime_plan_set_timing_events")
 
     def set_main_events(self, start=None, stop=None):
-        """torch.cuda.Event pair recorded around the per-baseline kernel alone
-        (same creation rule as set_timing_events)."""
+        """torch.cuda.Event pair recorded around the per-baseline kernel (or the
+        float64 engine's planes, forward and adjoint) alone; around all sets of
+        a batched call that runs set by set (same creation rule as
+        set_timing_events)."""
         for ev in (start, stop):
             if ev is not None and not ev.cuda_event:
                 raise ValueError("timing event has no hipEvent yet: record() it once first")

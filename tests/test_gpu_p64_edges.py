@@ -208,6 +208,31 @@ def test_smaller_skies_in_a_workspace_for_the_largest(prec):
     plan.close()
 
 
+def test_main_events_of_a_batch_by_sets():
+    """The main-event hooks bracket the engine's kernels of a batched call that
+    runs set by set: most of what the timing events bracket."""
+    obs, sky, D, W = problem(64, 12, 45, 64, 64, 0, "")
+    plan = R.Plan(obs)
+    batch = R.Batch(plan, [R.DeviceSky.from_host(sky) for _ in range(4)])
+    Dd, Wd = dev(D, W)
+    ws = torch.empty(batch.workspace_size(R.MODE_CHI2_GRAD, 0), dtype=torch.uint8, device="cuda")
+    chi2, grad = torch.empty(4, **F64), torch.empty((batch.total_src, 10), **F64)
+    R.rime_chi2_batched(batch, 0, Dd, Wd, chi2, grad, ws)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(4)]
+    for e in ev:
+        e.record()
+    torch.cuda.synchronize()
+    plan.set_timing_events(ev[0], ev[1])
+    plan.set_main_events(ev[2], ev[3])
+    R.rime_chi2_batched(batch, 0, Dd, Wd, chi2, grad, ws)
+    torch.cuda.synchronize()
+    plan.set_timing_events(None, None)
+    plan.set_main_events(None, None)
+    assert ev[2].elapsed_time(ev[3]) >= 0.5 * ev[0].elapsed_time(ev[1]) > 0.0
+    batch.close()
+    plan.close()
+
+
 def smallest_workspace(call, full):
     """Least bytes that `call(ws)` accepts."""
     lo, hi = 0, full  # refused, accepted
