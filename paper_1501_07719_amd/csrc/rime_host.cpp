@@ -546,7 +546,7 @@ WsLayout ws_layout(const rime_plan *plan, int mode, int prec, const Geometry &g,
         1, std::min<size_t>(std::min<int64_t>(plan->ntime, 65534), kPmePlaneBytes / per_t)));
     L.has_k3 = k3;
     L.ph_hi = off;
-    off += align_up(plane_t * (k3 ? 3 : 2) * L.pme_tchunk) + 4 * kAlign;
+    off += align_up(plane_t * (k3 ? 3 : 2) * L.pme_tchunk);
     if (fwd_sums) {
       L.spts = off;
       off += align_up(static_cast<size_t>(plan->ntime) * plan->nchan * plan->npair * 4 *
@@ -797,7 +797,8 @@ struct Call {
 // Divides the plane region of the fp16 engine: hi and lo planes of the point
 // sources (and their k3 in gradient mode), then the float32 planes of the
 // extended sources that rime_main stages from.  Both take the same bytes per
-// source, so the region, sized for the call's sources, holds any split.
+// source (a multiple of 128, so that no plane needs padding), and the region,
+// sized for the call's sources, holds any split.
 // Extended sources get planes in the forward-only modes of the 256-thread
 // kernels and in the gradient mode when one pass over time holds them all:
 // there every antenna's terms would be formed by (tiles per antenna)
@@ -820,9 +821,10 @@ void carve_planes(const rime_plan *plan, const Call &c, const Variant &v, const 
   size_t off = L.ph_hi;
   auto take = [&](size_t bytes) {
     char *r = w + off;
-    off += align_up(bytes);
+    off += bytes;
     return r;
   };
+  static_assert(kPmeBlk * sizeof(float) % 128 == 0, "rows of plan->nap antennas");
   p.ph_hi = reinterpret_cast<uint32_t *>(take(per_src * c.one.npsrc));
   p.ph_lo = reinterpret_cast<uint32_t *>(take(per_src * c.one.npsrc));
   if (L.has_k3) p.ph_k3 = reinterpret_cast<float *>(take(per_src * c.one.npsrc));

@@ -314,3 +314,29 @@ def test_workspace_of_the_engine_is_bounded():
     of all timesteps take 15 GB; a call asks for one pass over time."""
     n, = engine_sizes(64, 100, 64, [1500], 0, R.MODE_CHI2_GRAD)
     assert n <= 3 << 30
+
+
+@pytest.mark.parametrize("na,ntime,nchan,prec,n", [
+    (20, 3, 8, 1, 1811), (16, 5, 8, 1, 1047), (27, 5, 7, 2, 1194), (32, 1, 2, 2, 18272)])
+def test_largest_sky_of_the_fixed_workspace(na, ntime, nchan, prec, n):
+    """The float32 planes are packed: the most point sources that the library's
+    32 MiB hold beside the other regions."""
+    obs = make_problem("c1", ntime=ntime, nchan=nchan, npsrc=4, ngsrc=0, na=na, key=1,
+                       dense=False).obs
+    plan = R.Plan(obs)
+    shape = (ntime, plan.nbl, nchan, 4)
+    D = torch.zeros(shape, dtype=torch.complex64, device="cuda")
+    W = torch.ones(shape, dtype=torch.float32, device="cuda")
+    for k, fits in ((n, True), (2 * n, False)):
+        sky = R.DeviceSky(lm=torch.zeros((k, 2), **F64), stokes=torch.ones((k, 4), **F64),
+                          alpha=torch.zeros(k, **F64), gshape=torch.zeros((0, 3), **F64),
+                          npsrc=k, ngsrc=0)
+        chi2, grad = torch.empty(1, **F64), torch.full((k, 10), float("nan"), **F64)
+        if fits:
+            R.rime_chi2_grad_noalloc(plan, sky, prec, D, W, chi2, grad)
+            torch.cuda.synchronize()
+            assert torch.isfinite(grad).all()
+        else:
+            with pytest.raises(R.RimeError):
+                R.rime_chi2_grad_noalloc(plan, sky, prec, D, W, chi2, grad)
+    plan.close()
