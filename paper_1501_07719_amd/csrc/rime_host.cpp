@@ -1575,6 +1575,17 @@ rime_status rime_plan_create(const rime_obs_desc *obs, rime_plan **out) {
   }
   std::vector<double> pnt(static_cast<size_t>(obs->ntime) * obs->na * 2, 0.0);
   if (obs->beam == 1 && obs->pointing) std::copy(obs->pointing, obs->pointing + pnt.size(), pnt.begin());
+  // an antenna that no baseline holds may have undefined coordinates: kernels
+  // that work on whole antenna blocks weight its terms with sums of zero
+  std::vector<char> held(obs->na, 0);
+  for (int b = 0; b < obs->nbl; ++b) held[a1[b]] = held[a2[b]] = 1;
+  for (int t = 0; t < obs->ntime; ++t)
+    for (int a = 0; a < obs->na; ++a)
+      if (!held[a]) {
+        const size_t at = static_cast<size_t>(t) * obs->na + a;
+        std::fill_n(uvw.begin() + 3 * at, 3, 0.0);
+        std::fill_n(pnt.begin() + 2 * at, 2, 0.0);
+      }
   std::vector<double> gains(static_cast<size_t>(obs->na) * 4);
   for (int a = 0; a < obs->na; ++a) {
     for (int f = 0; f < 2; ++f) {

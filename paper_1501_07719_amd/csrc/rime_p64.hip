@@ -62,17 +62,13 @@ __global__ __launch_bounds__(256) void p64_planes(const KParams p) {
     }
     return;
   }
-  // an antenna without baselines may have undefined coordinates, and the
-  // adjoint weights its terms with sums of zero: the origin stands for it
-  const bool held = p.ant_off[a] != p.ant_off[a + 1];
-  auto at = [&](double x) { return held ? x : 0.0; };
   const double4 g = p.src_geo[s];
   const double *x = p.uvw + (static_cast<int64_t>(t) * p.na + a) * 3;
-  const PhaseArg<true> tau(at(x[0]), at(x[1]), at(x[2]), g.x, g.y, g.z);
+  const PhaseArg<true> tau(x[0], x[1], x[2], g.x, g.y, g.z);
   double r2b = 0.0, rb = 0.0;
   if (p.beam) {
     const double *q = p.pointing + (static_cast<int64_t>(t) * p.na + a) * 2;
-    r2b = sumsq_rn(g.x - at(q[0]), g.y - at(q[1]));
+    r2b = sumsq_rn(g.x - q[0], g.y - q[1]);
     rb = sqrt(r2b);
   }
   for (int c = cb; c < ce; ++c) {
@@ -415,30 +411,20 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
   // row masks, one per lane.  The coordinates of the 16 + 16 antennas are taken
   // from the first row's antenna that holds a baseline here: only differences
   // enter, and an offset common to all antennas would otherwise cost digits in
-  // the difference of the row and column sums.  Antennas without a baseline
-  // here (past the array, or with undefined coordinates) count as zero.
+  // the difference of the row and column sums.
   const uint32_t maskv = p.pair_mask[pair * kPmeBlk + si * 16 + (lane & 15)];
   {
     const int a = min((lane & 16 ? Q0 : P0) + (lane & 15), p.na - 1);
     const double *x = p.uvw + (static_cast<int64_t>(t) * p.na + a) * 3;
     const double *q = p.pointing + (static_cast<int64_t>(t) * p.na + a) * 2;
     const double u = x[0], v = x[1], w = x[2], ql = q[0], qm = q[1];
-    const uint32_t row = (maskv >> (sj * 16)) & 0xffffu;
-    const uint32_t rows = static_cast<uint32_t>(__ballot(row != 0u)) & 0xffffu;
-    // OR over each 16 lanes (rotations by 1, 2, 4 and 8 of a DPP row)
-    int cols = static_cast<int>(row);
-    cols |= __builtin_amdgcn_mov_dpp(cols, 0x121, 0xf, 0xf, true);
-    cols |= __builtin_amdgcn_mov_dpp(cols, 0x122, 0xf, 0xf, true);
-    cols |= __builtin_amdgcn_mov_dpp(cols, 0x124, 0xf, 0xf, true);
-    cols |= __builtin_amdgcn_mov_dpp(cols, 0x128, 0xf, 0xf, true);
-    const int first = __builtin_ctz(rows);
+    const uint64_t rows = __ballot(((maskv >> (sj * 16)) & 0xffffu) != 0u);
+    const int first = __builtin_ctzll(rows);
     const double u0 = lane_value(u, first), v0 = lane_value(v, first), w0 = lane_value(w, first);
-    const bool held = ((lane & 16 ? static_cast<uint32_t>(cols) : rows) >> (lane & 15)) & 1u;
-    const double2 zero = make_double2(0.0, 0.0);
     if (lane < 32) {
-      lds.ant[lane][0] = held ? make_double2(u - u0, v - v0) : zero;
-      lds.ant[lane][1] = held ? make_double2(w - w0, 0.0) : zero;
-      lds.ant[lane][2] = held ? make_double2(ql, qm) : zero;
+      lds.ant[lane][0] = make_double2(u - u0, v - v0);
+      lds.ant[lane][1] = make_double2(w - w0, 0.0);
+      lds.ant[lane][2] = make_double2(ql, qm);
     }
     lane_exchange();
   }
