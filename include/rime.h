@@ -98,7 +98,8 @@ typedef struct rime_obs_desc {
   const int32_t *ant2;       /* host [nbl] antenna q; NULL with ant1 NULL selects  */
                              /* the canonical p < q row-major order, nbl must then */
                              /* be na (na - 1) / 2                                */
-  const double *uvw;         /* host [ntime][na][3] metres                        */
+  const double *uvw;         /* host [ntime][na][3] metres; not read, like the    */
+                             /* pointing, for antennas that no baseline holds     */
   const double *freq;        /* host [nchan] Hz, > 0                              */
   double ref_freq;           /* spectral-index reference frequency, Hz, > 0       */
   int32_t beam;              /* 0: e = 1; 1: cos^3 beam with pointing errors      */

@@ -470,7 +470,7 @@ bool p64_active(const rime_plan *plan, const Variant &v, int prec, int nset, int
          p64_geometry(plan, mode, total_src).step <= kP64StepBytes;
 }
 
-// Chunks of adjoint items that the first pass of the engine's gradient sums forms.
+// Chunks of adjoint items that the engine's gradient sums keep from pass to pass.
 constexpr int kP64FinChunks = 64;
 
 // Words of the domain-flag header at the start of every workspace: a count,
@@ -833,8 +833,8 @@ void carve_planes(const rime_plan *plan, const Call &c, const Variant &v, const 
                          nat_for_host(v.threads) * plan->ntime * plan->nchan * next;
   const bool grad = c.mode == RIME_MODE_CHI2_GRAD;
   const bool k3 = grad && plan->beam;
-  if (staged >= (int64_t(1) << (grad ? 21 : 24)) && L.pme_tchunk >= plan->ntime && plan->nchan <= (1 << 17) &&
-      v.nc == 2 &&
+  if (staged >= (int64_t(1) << (grad ? 21 : 24)) && L.pme_tchunk >= plan->ntime &&
+      plan->nchan <= (1 << 17) && v.nc == 2 &&
       (grad ? L.pme_adj && c.prec == RIME_MIXED && !c.die && !c.stokes_t : v.threads == 256)) {
     p.pl_s0 = c.one.npsrc;
     p.pl_ns = next;

@@ -40,9 +40,10 @@ __device__ void prep_slots(const KParams &p, int t);
 // (eq. brightness_term) and the Gaussian shape coefficients, one thread per
 // source and block of kPrepCh channels (blockIdx.z; with all channels in one
 // thread their exponentials formed a serial chain: 75 sources, 16 channels
-// 9.9 us, 2000 sources, 256 channels 123 us); each workgroup also records whether one of its sources lies outside
-// the domain l^2 + m^2 < 1 of n = sqrt(1 - l^2 - m^2) (Section 2.1, after
-// eq. k_term), whose geometry is then NaN.  Rows nset + t (gradient mode,
+// 9.9 us, 2000 sources, 256 channels 123 us); each workgroup also records
+// whether one of its sources lies outside the domain l^2 + m^2 < 1 of
+// n = sqrt(1 - l^2 - m^2) (Section 2.1, after eq. k_term), whose geometry is
+// then NaN.  Rows nset + t (gradient mode,
 // nc > 0): the adjoint's per-baseline records of timestep t.
 // ---------------------------------------------------------------------------
 constexpr int kPrepCh = 8;

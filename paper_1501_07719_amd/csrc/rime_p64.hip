@@ -1,12 +1,13 @@
 // Float64 engine of one sky over large arrays (gfx950).
 //
 //   p64_planes    a_ps = e_ps K_ps (and the beam-gradient factor k3) of every
-//                 (timestep, channel, source, antenna), once per call, in HBM;
+//                 (timestep, channel, source, antenna), once per call, in HBM,
+//                 for one pass over time after the other;
 //   p64_forward   source sums, visibilities, chi^2 and residual of 16 x 16
 //                 antenna sub-blocks;
 //   p64_adjoint   the gradient sums of 64 sources over one sub-block;
-//   p64_fin_items, p64_finalize
-//                 the sums of the adjoint's partials.
+//   p64_fin_items, p64_stokes_t, p64_finalize
+//                 the sums of the adjoint's partials, the first two per pass.
 //
 // The per-baseline kernel (rime_main) forms every antenna's terms in each
 // workgroup whose tile holds the antenna, which took half of its float64
@@ -18,12 +19,14 @@
 // and holds eight antennas in registers, the residual coming as LDS
 // broadcasts.
 //
-// Bound by float64 instruction issue (the chip holds about 1.9 GHz under them).
-// 64 antennas, 100 timesteps, 64 channels, 1000 points + 500 Gaussians, beam:
-//   planes 2.9 ms (3.4 ms with k3), forward 17.4 ms (12 instructions per point term
-//   and 37 per Gaussian term, 76 % of issue slots used), adjoint 18.2 ms for
-//   the points (28 per term, 77 %) and 17.0 ms for the Gaussians (61, 80 %);
-//   chi^2 + gradient 56.1 ms, chi^2 19.6 ms, against 88.5 and 27.3 ms on the
+// Bound by float64 instruction issue (the chip holds 1.9 to 2.0 GHz under them).
+// 64 antennas, 100 timesteps, 64 channels, 1000 points + 500 Gaussians, beam,
+// sums over the passes of a call:
+//   planes 2.1 ms (2.7 ms with k3), forward 18.4 ms (12 instructions per point
+//   term and 37 per Gaussian term in the loops, 22.8 per term in all, 72 to 76 %
+//   of the issue slots used), adjoint 17.8 ms for the points (28 in the loop,
+//   33.7 in all, 75 %) and 17.3 ms for the Gaussians (61, 68.9, 77 %);
+//   chi^2 + gradient 57.0 ms, chi^2 20.0 ms, against 88.7 and 28.0 ms on the
 //   per-baseline kernel.
 // Measured and not kept: point-source sums on v_mfma_f64_16x16x4_f64 (forward
 // 9.4 ms for the points alone; float64 matrix and vector instructions have the
@@ -369,11 +372,12 @@ __global__ __launch_bounds__(256, 2) void p64_forward(const KParams p) {
 
 // ---------------------------------------------------------------------------
 // Adjoint: wavefront = (64 sources of one morphology, timestep, p.p64_ncw
-// channels, sub-block or, in small calls, an eighth of one); lane = source.  The sub-block's columns are taken
-// eight at a time: their antenna terms and their sums of Re P and Im P
-// (P = c sum_k St'_k rho_k) stay in registers, the rows pass by, and the
-// residual and baseline vector of a slot are scalar.  With the row and column
-// sums of P the position gradient needs no per-baseline factor:
+// channels, sub-block or, in small calls, an eighth of one); lane = source.
+// The sub-block's columns are taken eight at a time: their antenna terms and
+// their sums of Re P and Im P (P = c sum_k St'_k rho_k) stay in registers, the
+// rows pass by, and the residual and baseline vector of a slot come as LDS
+// broadcasts.  With the row and column sums of P the position gradient needs no
+// per-baseline factor:
 //   sum (u_p - u_q) Im P        = sum_p u_p row_p - sum_q u_q col_q
 //                                 (u from an origin inside the sub-block),
 //   sum (beta_p + beta_q) Re P  = sum_p beta_p row_p + sum_q beta_q col_q.
@@ -631,7 +635,7 @@ __device__ inline void p64_adj_item(const KParams &p, int sub, int part, int t, 
 // SHAPED: the groups of Gaussians and disks, else those of point sources (two
 // kernels, since the point sources need fewer registers).  Consecutive
 // wavefronts take the source groups of one (timestep, channel group,
-// sub-block), whose residual they read through the scalar cache.
+// sub-block), whose residual they share in L2.
 template <bool SHAPED, bool ST>
 __global__ __launch_bounds__(256, 2) void p64_adjoint(const KParams p) {
   __shared__ AdjLds s_lds[4];
