@@ -1579,13 +1579,12 @@ rime_status rime_plan_create(const rime_obs_desc *obs, rime_plan **out) {
   // that work on whole antenna blocks weight its terms with sums of zero
   std::vector<char> held(obs->na, 0);
   for (int b = 0; b < obs->nbl; ++b) held[a1[b]] = held[a2[b]] = 1;
-  for (int t = 0; t < obs->ntime; ++t)
-    for (int a = 0; a < obs->na; ++a)
-      if (!held[a]) {
-        const size_t at = static_cast<size_t>(t) * obs->na + a;
-        std::fill_n(uvw.begin() + 3 * at, 3, 0.0);
-        std::fill_n(pnt.begin() + 2 * at, 2, 0.0);
-      }
+  for (int a = 0; a < obs->na; ++a)
+    for (int t = 0; t < obs->ntime && !held[a]; ++t) {
+      const size_t at = static_cast<size_t>(t) * obs->na + a;
+      std::fill_n(uvw.begin() + 3 * at, 3, 0.0);
+      std::fill_n(pnt.begin() + 2 * at, 2, 0.0);
+    }
   std::vector<double> gains(static_cast<size_t>(obs->na) * 4);
   for (int a = 0; a < obs->na; ++a) {
     for (int f = 0; f < 2; ++f) {

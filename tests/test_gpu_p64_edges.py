@@ -69,6 +69,26 @@ def test_antennas_without_baselines(dead, beam):
     check(gradient(obs, sky, D, W), gradient(obs, sky, D, W, 0), sky)
 
 
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_dropped_antennas_are_not_read(prec):
+    """Undefined coordinates of antennas without baselines give the bits that any
+    others give, in every precision."""
+    obs, sky, D, W = problem(40, 2, 4, 70, 40, 20, "")
+    dead = [2, 31, 39]
+    keep = ~(np.isin(obs.ant1, dead) | np.isin(obs.ant2, dead))
+    D, W = np.ascontiguousarray(D[:, keep]), np.ascontiguousarray(W[:, keep])
+    out = []
+    for x in (1.0, np.nan):
+        uvw, pnt = obs.uvw.copy(), obs.pointing.copy()
+        uvw[:, dead] *= x
+        pnt[:, dead] *= x
+        o = Observation(**{**obs.__dict__, "ant1": obs.ant1[keep], "ant2": obs.ant2[keep],
+                           "uvw": uvw, "pointing": pnt})
+        out.append(gradient(o, sky, D, W, prec=prec))
+    assert np.isfinite(out[0][1]).all() and out[0][0] == out[1][0]
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("ng", [0, 40])
 def test_common_offset_of_the_antenna_coordinates(ng):
     """Only coordinate differences enter the model; antennas given from the
